@@ -26,11 +26,28 @@ struct IonTables {
 };
 
 // Ionisation counters (unsigned long long): [CNT_FALLBACK] is the length of
-// the fallback list; the active-ion and event counts are striped over
-// CNT_STRIPES words each (supercell sc adds to word sc % CNT_STRIPES) so that
-// thousands of workgroups do not serialise on one address; the host sums them.
+// the fallback list; the active-ion, event and fallback-ion counts are striped
+// over CNT_STRIPES words each (supercell sc adds to word sc % CNT_STRIPES) so
+// that thousands of workgroups do not serialise on one address; the host sums them.
 constexpr int CNT_FALLBACK = 2, CNT_STRIPES = 64;
-constexpr int CNT_ACTIVE = 8, CNT_FIRED = CNT_ACTIVE + CNT_STRIPES, CNT_WORDS = CNT_FIRED + CNT_STRIPES;
+constexpr int CNT_ACTIVE = 8, CNT_FIRED = CNT_ACTIVE + CNT_STRIPES, CNT_FBIONS = CNT_FIRED + CNT_STRIPES,
+              CNT_WORDS = CNT_FBIONS + CNT_STRIPES;
+
+// The rate depends on an ion's cell and charge state only, so a step rates
+// the distinct (cell, Z) pairs its ions occupy, not the ions: per supercell,
+// pair i holds cell | Z << 8 (cells in order, states ascending in a cell), and
+// cell c's pairs start at off(info) and follow the bits of mask(info),
+// info = off << PAIR_MASK_BITS | mask.
+constexpr int PAIR_MASK_BITS = 16;
+static_assert(PIC_MAX_ZSTATES <= PAIR_MASK_BITS, "one mask bit per charge state");
+struct PairBuffers {
+    int cap;             // pairs per supercell: 256 z_max
+    uint16_t* list;      // [nsc][cap]
+    uint32_t* info;      // [nsc][256]
+    int32_t* count;      // [nsc]
+    uint8_t* cell;       // [nsc][ion.cap]: the cell of every ion with Z < z_max
+    double* nu;          // [nsc][cap] rates (1/s); the sign bit marks those of the exact fallback
+};
 
 struct DrawArgs {
     uint64_t seed;
@@ -57,9 +74,9 @@ struct DrawBuffers {
 constexpr int RATE_TABLE_N = 1024;
 constexpr double RATE_TABLE_TMIN = 1e-2, RATE_TABLE_TMAX = 1e6;
 hipError_t launch_rate_table_build(const IonTables& tab, const double* gl, double* table, hipStream_t st);
-// fb_list: one entry per ion slot, for the ions outside the table's range
-hipError_t launch_rate_table(const GridView& g, const SpeciesView& ion, const IonTables& tab, const double* ne,
-                             const double* kT, double* nu, const double* table, const double* gl,
+// fb_list: one entry per pair, for the pairs outside the table's range
+hipError_t launch_rate_table(const GridView& g, const PairBuffers& pb, const IonTables& tab, const double* ne,
+                             const double* kT, const double* table, const double* gl,
                              unsigned long long* counters, unsigned long long* fb_list, hipStream_t st);
 hipError_t launch_ln_rate_table(int64_t n, const double* kT, const double* ne, const int32_t* Z, const IonTables& tab,
                                 const double* table, const double* gl, double* out, hipStream_t st);
@@ -70,13 +87,17 @@ const double* gauss_laguerre_nodes(const double** w);
 // mom4: per cell (sum w, mean ux, uy, uz), or nullptr
 hipError_t launch_moments(const GridView& g, const SpeciesView& e, double n_ref_over_dv, double* ne, double* kT,
                           double* mom4, hipStream_t st);
-hipError_t launch_rate_exact(const GridView& g, const SpeciesView& ion, const IonTables& tab, const double* ne,
-                             const double* kT, double* nu, const double* gl, hipStream_t st);
+// ... and the (cell, Z) pairs of the ions with Z < z_max
+hipError_t launch_moments_pairs(const GridView& g, const SpeciesView& e, const SpeciesView& ion, int z_max,
+                                const PairBuffers& pb, double n_ref_over_dv, double* ne, double* kT, double* mom4,
+                                hipStream_t st);
+hipError_t launch_rate_exact(const GridView& g, const PairBuffers& pb, const IonTables& tab, const double* ne,
+                             const double* kT, const double* gl, hipStream_t st);
 hipError_t launch_ln_rate_exact(int64_t n, const double* kT, const double* ne, const int32_t* Z, const IonTables& tab,
                                 const double* gl, double* out, hipStream_t st);
 hipError_t launch_draw_append(const GridView& g, const SpeciesView& ion, const SpeciesView& el, const IonTables& tab,
-                              const DrawArgs& a, const double* nu, const DrawBuffers& b, unsigned long long* counters,
-                              hipStream_t st);
+                              const DrawArgs& a, const PairBuffers& pb, const DrawBuffers& b,
+                              unsigned long long* counters, hipStream_t st);
 hipError_t launch_energy_loss(const GridView& g, const SpeciesView& el, const DrawBuffers& b, hipStream_t st);
 // The step with the exact rate fused (moments, rate, draw and append per
 // supercell in one kernel); ne, kT (and mom4) receive the cell moments as
@@ -104,13 +125,14 @@ struct MlpStep {
     int64_t step;
     int act;               // PIC_MLP_SILU or PIC_MLP_RELU
 };
-// fb_list: one entry per ion slot (nsc * cap), for the out-of-range ions
-hipError_t launch_rate_mlp(const GridView& g, const SpeciesView& ion, const IonTables& tab, const MlpLaunch& ml,
-                           const double* ne, const double* kT, double* nu, const double* gl,
-                           unsigned long long* counters, unsigned long long* fb_list, hipStream_t st);
-// The exact FP64 rate for the counters[2] ions listed in fb_list.
-hipError_t launch_rate_fallback(const GridView& g, const SpeciesView& ion, const IonTables& tab, const double* ne,
-                                const double* kT, double* nu, const double* gl, const unsigned long long* fb_list,
+// fb_list: one entry per pair, for the out-of-range pairs
+hipError_t launch_rate_mlp(const GridView& g, const PairBuffers& pb, const IonTables& tab, const MlpLaunch& ml,
+                           const double* ne, const double* kT, const double* gl, unsigned long long* counters,
+                           unsigned long long* fb_list, hipStream_t st);
+// The exact FP64 rate, with the sign bit set, for the counters[CNT_FALLBACK]
+// pairs listed in fb_list.
+hipError_t launch_rate_fallback(const GridView& g, const PairBuffers& pb, const IonTables& tab, const double* ne,
+                                const double* kT, const double* gl, const unsigned long long* fb_list,
                                 const unsigned long long* counters, hipStream_t st);
 hipError_t launch_ln_rate_mlp(int64_t n, const double* kT, const double* ne, const int32_t* Z, const IonTables& tab,
                               const MlpLaunch& ml, const double* gl, double* out, hipStream_t st);
@@ -177,6 +199,35 @@ __device__ inline double lotz_shells(double kT, const IonTables& t, int Z, const
     return acc;
 }
 
+// lotz_shells by a group of four consecutive lanes that hold the same kT and Z:
+// lane j of the group takes the nodes j, j + 4, ..., and the four partial sums
+// are added so that every lane returns the same total.
+__device__ inline double lotz_shells4(double kT, const IonTables& t, int Z, const double* glx, const double* glw)
+{
+    const int j4 = threadIdx.x & 3;
+    double acc = 0.0;
+    for (int j = 0; j < t.ns[Z]; ++j) {
+        const double p = t.sp[Z][j], r = kT / p, b = t.sb[Z][j], c = t.sc[Z][j];
+        double s = 0.0;
+        if (b == 0.0) {
+#pragma unroll 8
+            for (int k = j4; k < GL_NODES; k += 4) s = fma(glw[k], log1p(glx[k] * r), s);
+        } else {
+#pragma unroll 4
+            for (int k = j4; k < GL_NODES; k += 4) {
+                const double xr = glx[k] * r;
+                s = fma(glw[k] * log1p(xr), 1.0 - b * exp(-c * xr), s);
+            }
+        }
+        s += __shfl_xor(s, 1, 64);
+        s += __shfl_xor(s, 2, 64);
+        double v = t.aq[Z][j] / p * s;
+        if (j > 0) v *= exp(-(p - t.P[Z]) / kT);
+        acc += v;
+    }
+    return acc;
+}
+
 __device__ inline double vbar_cm_s(double kT) { return C_CM_S * sqrt(8.0 * kT / (M_PI * ME_C2_EV)); }
 
 __device__ inline double rate_exact(double kT, double ne, const IonTables& t, int Z, const double* glx,
@@ -184,6 +235,14 @@ __device__ inline double rate_exact(double kT, double ne, const IonTables& t, in
 {
     if (!(kT > 0.0) || !(ne > 0.0)) return 0.0;
     return ne * vbar_cm_s(kT) / kT * exp(-t.P[Z] / kT) * lotz_shells(kT, t, Z, glx, glw);
+}
+
+// rate_exact by a group of four lanes (lotz_shells4)
+__device__ inline double rate_exact4(double kT, double ne, const IonTables& t, int Z, const double* glx,
+                                     const double* glw)
+{
+    if (!(kT > 0.0) || !(ne > 0.0)) return 0.0;
+    return ne * vbar_cm_s(kT) / kT * exp(-t.P[Z] / kT) * lotz_shells4(kT, t, Z, glx, glw);
 }
 
 __device__ inline double ln_rate_exact(double kT, double ne, const IonTables& t, int Z, const double* glx,

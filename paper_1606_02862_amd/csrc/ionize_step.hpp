@@ -83,6 +83,61 @@ __device__ inline void moments_store(const CellMoments& c, int64_t gi, double* n
     }
 }
 
+// ---------------------------------------------------------------- pairs
+// The supercell's distinct (cell, Z) pairs: one thread per cell.
+struct PairLds {
+    unsigned mask[SC_CELLS];   // charge states below z_max present in the cell
+    int off[SC_CELLS];         // the cell's first pair
+    int wsum[BLOCK / 64];
+};
+
+__device__ inline int ion_cell(const SpeciesView& ion, int64_t p)
+{
+    return (int)ion.x[p] + SX * ((int)ion.y[p] + SY * (int)ion.z[p]);
+}
+
+// Marks the pairs of the supercell's ions (and keeps every ion's cell in
+// `cell`, when given) and lists them through put(i, cell, Z).  Every thread of
+// the workgroup calls it; it ends with a barrier.  Returns the pair count.
+template <class Put>
+__device__ inline int pairs_build(const SpeciesView& ion, int sc, int z_max, PairLds& pl, uint8_t* cell, Put put)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    pl.mask[tid] = 0u;
+    __syncthreads();
+    const int n = ion.count[sc];
+    const int64_t base = (int64_t)sc * ion.cap;
+#pragma unroll 4
+    for (int t = tid; t < n; t += BLOCK) {
+        const int Z = ion.zs[base + t];
+        const int c = ion_cell(ion, base + t);
+        if (Z < z_max) atomicOr(&pl.mask[c], 1u << Z);
+        if (cell) cell[base + t] = (uint8_t)c;
+    }
+    __syncthreads();
+    const unsigned m = pl.mask[tid];
+    const int k = __popc(m);
+    int incl = k;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+    }
+    if (lane == 63) pl.wsum[wave] = incl;
+    __syncthreads();
+    int before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < BLOCK / 64; ++w) {
+        if (w < wave) before += pl.wsum[w];
+        total += pl.wsum[w];
+    }
+    int i = before + incl - k;
+    pl.off[tid] = i;
+    for (unsigned r = m; r; r &= r - 1) put(i++, tid, __ffs((int)r) - 1);
+    __syncthreads();
+    return total;
+}
+
 // ---------------------------------------------------------------- events
 __device__ inline uint64_t word(const Philox4& r, int e)
 {
@@ -186,7 +241,7 @@ __device__ inline int append_events(const SpeciesView& ion, const SpeciesView& e
 
 // Per-supercell bookkeeping of the draw, in LDS.
 struct DrawLds {
-    int add, fired, active;
+    int add, fired, active, fb;
 };
 
 // After the supercell's last append (behind a barrier): its electron count,
@@ -199,6 +254,7 @@ __device__ inline void draw_finish(const SpeciesView& el, const DrawArgs& a, con
     el.count[sc] = ebase + added;
     if (a.energy_loss) db.old_count[sc] = ebase;
     if (d.fired) atomicAdd(&counters[CNT_FIRED + sc % CNT_STRIPES], (unsigned long long)d.fired);
+    if (d.fb) atomicAdd(&counters[CNT_FBIONS + sc % CNT_STRIPES], (unsigned long long)d.fb);
 }
 
 }  // namespace pic

@@ -28,35 +28,59 @@ hipError_t launch_moments(const GridView& g, const SpeciesView& e, double n_ref_
     return hipGetLastError();
 }
 
+// The moments of the staged step and, per supercell, the (cell, Z) pairs that
+// the rate stage rates and the cell of every ion for the draw.
+__global__ __launch_bounds__(BLOCK) void k_moments_pairs(GridView g, SpeciesView e, SpeciesView ion, int z_max,
+                                                         PairBuffers pb, double n_ref_over_dv, double* ne, double* kT,
+                                                         double* mom4)
+{
+    __shared__ MomLds m;
+    __shared__ PairLds pl;
+    const int sc = blockIdx.x, tid = threadIdx.x;
+    moments_accumulate(e, sc, m);
+    moments_store(moments_cell(m, tid, n_ref_over_dv), cell_index(g, sc, tid), ne, kT, mom4);
+    uint16_t* const list = pb.list + (int64_t)sc * pb.cap;
+    const int np = pairs_build(ion, sc, z_max, pl, pb.cell,
+                               [&](int i, int c, int Z) { list[i] = (uint16_t)(c | Z << 8); });
+    pb.info[(int64_t)sc * SC_CELLS + tid] = (uint32_t)pl.off[tid] << PAIR_MASK_BITS | pl.mask[tid];
+    if (tid == 0) pb.count[sc] = np;
+}
+
+hipError_t launch_moments_pairs(const GridView& g, const SpeciesView& e, const SpeciesView& ion, int z_max,
+                                const PairBuffers& pb, double n_ref_over_dv, double* ne, double* kT, double* mom4,
+                                hipStream_t st)
+{
+    if (pb.cap < SC_CELLS * z_max) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_moments_pairs, dim3(g.nsc), dim3(BLOCK), 0, st, g, e, ion, z_max, pb, n_ref_over_dv, ne, kT,
+                       mom4);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- exact rate
-__global__ __launch_bounds__(BLOCK) void k_rate_exact(GridView g, SpeciesView ion, IonTables tab, const double* ne,
-                                                      const double* kT, double* nu, const double* gl)
+// The quadrature of every pair, four lanes each: FP64 ALU bound.  Rating the
+// pairs instead of the ions divides the work by the ions per cell and state.
+__global__ __launch_bounds__(BLOCK) void k_rate_exact(GridView g, PairBuffers pb, IonTables tab, const double* ne,
+                                                      const double* kT, const double* gl)
 {
     __shared__ double glx[GL_NODES], glw[GL_NODES];
     const int sc = blockIdx.x;
     const int tid = threadIdx.x;
     if (tid < GL_NODES) { glx[tid] = gl[tid]; glw[tid] = gl[GL_NODES + tid]; }
     __syncthreads();
-    const int n = ion.count[sc];
-    const int64_t base = (int64_t)sc * ion.cap;
-    const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
-    for (int t = tid; t < n; t += BLOCK) {
-        const int64_t p = base + t;
-        const int Z = ion.zs[p];
-        double v = 0.0;
-        if (Z < tab.z_max) {
-            const int64_t gi = (int64_t)(scx * SX + (int)ion.x[p]) +
-                               (int64_t)g.nx * ((scy * SY + (int)ion.y[p]) + (int64_t)g.ny * (scz * SZ + (int)ion.z[p]));
-            v = rate_exact(kT[gi], ne[gi], tab, Z, glx, glw);
-        }
-        nu[p] = v;
+    const int n = pb.count[sc];
+    const int64_t base = (int64_t)sc * pb.cap;
+    for (int i = tid >> 2; i < n; i += BLOCK / 4) {
+        const int pr = pb.list[base + i];
+        const int64_t gi = cell_index(g, sc, pr & 255);
+        const double v = rate_exact4(kT[gi], ne[gi], tab, pr >> 8, glx, glw);
+        if ((tid & 3) == 0) pb.nu[base + i] = v;
     }
 }
 
-hipError_t launch_rate_exact(const GridView& g, const SpeciesView& ion, const IonTables& tab, const double* ne,
-                             const double* kT, double* nu, const double* gl, hipStream_t st)
+hipError_t launch_rate_exact(const GridView& g, const PairBuffers& pb, const IonTables& tab, const double* ne,
+                             const double* kT, const double* gl, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_rate_exact, dim3(g.nsc), dim3(BLOCK), 0, st, g, ion, tab, ne, kT, nu, gl);
+    hipLaunchKernelGGL(k_rate_exact, dim3(g.nsc), dim3(BLOCK), 0, st, g, pb, tab, ne, kT, gl);
     return hipGetLastError();
 }
 
@@ -93,41 +117,51 @@ hipError_t launch_ln_rate_exact(int64_t n, const double* kT, const double* ne, c
 // CHAIN: max_events > 1 (the instantiation for one event carries no quadrature).
 template <bool CHAIN>
 __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView ion, SpeciesView el, IonTables tab,
-                                                       DrawArgs a, const double* nu, DrawBuffers db,
+                                                       DrawArgs a, PairBuffers pb, DrawBuffers db,
                                                        unsigned long long* counters)
 {
     __shared__ double glx[GL_NODES], glw[GL_NODES];
     __shared__ DrawLds s_d;
+    __shared__ uint32_t s_info[SC_CELLS];  // the cells' pairs
     const int sc = blockIdx.x;
     const int tid = threadIdx.x;
     if (CHAIN && tid < GL_NODES) { glx[tid] = db.gl[tid]; glw[tid] = db.gl[GL_NODES + tid]; }
-    if (tid == 0) s_d = DrawLds{0, 0, 0};
+    if (tid == 0) s_d = DrawLds{0, 0, 0, 0};
+    s_info[tid] = pb.info[(int64_t)sc * SC_CELLS + tid];
     __syncthreads();
     const int n = ion.count[sc];
     const int ebase = el.count[sc];
     const int room = el.cap - ebase;
     const int64_t base = (int64_t)sc * ion.cap;
-    const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
+    const double* const nu = pb.nu + (int64_t)sc * pb.cap;
     bool full = false;
-    int fired = 0, active = 0;
+    int fired = 0, active = 0, fb = 0;
     // chunks of DRAW_PER slots per lane: every load of a chunk is issued
     // before the first decision, so the lanes wait on memory once per chunk
     constexpr int DRAW_PER = 4;
     for (int c0 = 0; c0 < n; c0 += BLOCK * DRAW_PER) {
-        int zs[DRAW_PER];
+        int zs[DRAW_PER], cells[DRAW_PER];
         uint32_t ids[DRAW_PER];
         double nus[DRAW_PER];
 #pragma unroll
         for (int k = 0; k < DRAW_PER; ++k) {
             const int t = c0 + k * BLOCK + tid;
             zs[k] = tab.z_max;  // inactive
+            cells[k] = 0;
             ids[k] = 0;
-            nus[k] = 0.0;
             if (t < n) {
                 const int64_t p = base + t;
                 zs[k] = ion.zs[p];
+                cells[k] = pb.cell[p];
                 ids[k] = ion.id[p];
-                nus[k] = nu[p];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < DRAW_PER; ++k) {
+            nus[k] = 0.0;
+            if (zs[k] < tab.z_max) {
+                const uint32_t info = s_info[cells[k]];
+                nus[k] = nu[(info >> PAIR_MASK_BITS) + __popc(info & ((1u << zs[k]) - 1u))];
             }
         }
 #pragma unroll
@@ -138,12 +172,11 @@ __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView i
             int64_t gi = 0;
             if (Z0 < tab.z_max) {
                 ++active;
+                fb += signbit(nus[k]) ? 1 : 0;  // rated by the exact fallback
                 // the ion's cell, for later events' rates and the energy account only
-                if (CHAIN || a.energy_loss)
-                    gi = (int64_t)(scx * SX + (int)ion.x[p]) +
-                         (int64_t)g.nx * ((scy * SY + (int)ion.y[p]) + (int64_t)g.ny * (scz * SZ + (int)ion.z[p]));
-                nev = ion_events<CHAIN>(tab, a, ids[k], Z0, nus[k], CHAIN ? db.kT[gi] : 0.0, CHAIN ? db.ne[gi] : 0.0,
-                                        glx, glw);
+                if (CHAIN || a.energy_loss) gi = cell_index(g, sc, cells[k]);
+                nev = ion_events<CHAIN>(tab, a, ids[k], Z0, fabs(nus[k]), CHAIN ? db.kT[gi] : 0.0,
+                                        CHAIN ? db.ne[gi] : 0.0, glx, glw);
             }
             const int b = wave_reserve<CHAIN>(nev, &s_d.add);  // every lane of the wave
             if (nev) fired += append_events(ion, el, tab, a, db.de, sc, p, gi, ids[k], Z0, nev, b, ebase, room, full);
@@ -152,38 +185,43 @@ __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView i
     if (full) g.flags[FLAG_CAPACITY] = 1;
     if (fired) atomicAdd(&s_d.fired, fired);
     if (active) atomicAdd(&s_d.active, active);
+    if (fb) atomicAdd(&s_d.fb, fb);
     __syncthreads();
     if (tid == 0) draw_finish(el, a, db, sc, ebase, room, s_d, counters);
 }
 
 hipError_t launch_draw_append(const GridView& g, const SpeciesView& ion, const SpeciesView& el, const IonTables& tab,
-                              const DrawArgs& a, const double* nu, const DrawBuffers& b, unsigned long long* counters,
-                              hipStream_t st)
+                              const DrawArgs& a, const PairBuffers& pb, const DrawBuffers& b,
+                              unsigned long long* counters, hipStream_t st)
 {
     if (a.energy_loss && (!b.de || !b.old_count || !b.mom4)) return hipErrorInvalidValue;
     if (a.max_events > 1)
-        hipLaunchKernelGGL(k_draw_append<true>, dim3(g.nsc), dim3(BLOCK), 0, st, g, ion, el, tab, a, nu, b, counters);
+        hipLaunchKernelGGL(k_draw_append<true>, dim3(g.nsc), dim3(BLOCK), 0, st, g, ion, el, tab, a, pb, b, counters);
     else
-        hipLaunchKernelGGL(k_draw_append<false>, dim3(g.nsc), dim3(BLOCK), 0, st, g, ion, el, tab, a, nu, b, counters);
+        hipLaunchKernelGGL(k_draw_append<false>, dim3(g.nsc), dim3(BLOCK), 0, st, g, ion, el, tab, a, pb, b, counters);
     return hipGetLastError();
 }
 
 // One ionisation step of one ion species with the exact rate, fused per
 // supercell (one workgroup each): the electron moments of its cells in LDS
-// (written to the grid as well), then for each of its ions the exact rate
-// from its cell's moments and the draw and append of its events.
+// (written to the grid as well), the exact rate of each (cell, Z) pair that
+// its ions occupy, four lanes each, and for each ion the draw and append of
+// its events.
 template <bool CHAIN>
 __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView ion, SpeciesView el, IonTables tab,
                                                         DrawArgs a, DrawBuffers db, double n_ref_over_dv, double* ne,
                                                         double* kT, double* mom4, unsigned long long* counters)
 {
     __shared__ MomLds mom;
+    __shared__ PairLds pl;
+    __shared__ uint16_t s_list[SC_CELLS * PIC_MAX_ZSTATES];
+    __shared__ double s_nu[SC_CELLS * PIC_MAX_ZSTATES];
     __shared__ double glx[GL_NODES], glw[GL_NODES];
     __shared__ DrawLds s_d;
     const int sc = blockIdx.x;
     const int tid = threadIdx.x;
     if (tid < GL_NODES) { glx[tid] = db.gl[tid]; glw[tid] = db.gl[GL_NODES + tid]; }
-    if (tid == 0) s_d = DrawLds{0, 0, 0};
+    if (tid == 0) s_d = DrawLds{0, 0, 0, 0};
     moments_accumulate(el, sc, mom);  // its barriers also publish the rule and the reset above
     {
         // each thread reads and rewrites only its own cell's column
@@ -191,6 +229,13 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
         moments_store(cm, cell_index(g, sc, tid), ne, kT, mom4);
         mom.acc[0][tid] = cm.ne;
         mom.acc[1][tid] = cm.kT;
+    }
+    const int np = pairs_build(ion, sc, tab.z_max, pl, nullptr,
+                               [&](int i, int c, int Z) { s_list[i] = (uint16_t)(c | Z << 8); });
+    for (int i = tid >> 2; i < np; i += BLOCK / 4) {
+        const int pr = s_list[i], c = pr & 255;
+        const double v = rate_exact4(mom.acc[1][c], mom.acc[0][c], tab, pr >> 8, glx, glw);
+        if ((tid & 3) == 0) s_nu[i] = v;
     }
     __syncthreads();
     const int n = ion.count[sc];
@@ -207,9 +252,9 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
         uint32_t id = 0;
         if (Z < tab.z_max) {
             ++active;
-            cell = (int)ion.x[p] + SX * ((int)ion.y[p] + SY * (int)ion.z[p]);
+            cell = ion_cell(ion, p);
             const double cne = mom.acc[0][cell], ckT = mom.acc[1][cell];
-            const double nu0 = rate_exact(ckT, cne, tab, Z, glx, glw);
+            const double nu0 = s_nu[pl.off[cell] + __popc(pl.mask[cell] & ((1u << Z) - 1u))];
             id = ion.id[p];
             nev = ion_events<CHAIN>(tab, a, id, Z, nu0, ckT, cne, glx, glw);
         }

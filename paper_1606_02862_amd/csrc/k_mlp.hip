@@ -17,7 +17,7 @@
 // 16x16x32 over the hidden units), the small layers on VALU; gradients are
 // summed per wave in registers / LDS and added to a global accumulator once
 // per wave; Adam updates FP32 master weights.
-#include "ionize_internal.hpp"
+#include "ionize_step.hpp"
 
 namespace pic {
 
@@ -259,16 +259,15 @@ struct MlpArgs {
 };
 
 
-// Per supercell of ions: nu[p] for every ion (0 for Z >= z_max).  Ions whose
-// inputs lie outside the trained range are appended to `fb_list` (their
-// count in counters[CNT_FALLBACK]) and take the exact FP64 quadrature in a second,
+// The rate of every (cell, Z) pair of a supercell.  Pairs whose inputs lie
+// outside the trained range are appended to `fb_list` (their count in
+// counters[CNT_FALLBACK]) and take the exact FP64 quadrature in a second,
 // small kernel, so that the quadrature's registers do not lower this
-// kernel's occupancy.  Persistent workgroups
-// (weights loaded once); a wave takes 64 ions of a supercell at a time, one
-// per lane.
+// kernel's occupancy.  Persistent workgroups (weights loaded once); a wave
+// takes 64 pairs of a supercell at a time, one per lane.
 template <int ACT>
-__global__ __launch_bounds__(BLOCK) void k_rate_mlp(GridView g, SpeciesView ion, IonTables tab, MlpArgs m,
-                                                    const double* ne, const double* kT, double* nu,
+__global__ __launch_bounds__(BLOCK) void k_rate_mlp(GridView g, PairBuffers pb, IonTables tab, MlpArgs m,
+                                                    const double* ne, const double* kT,
                                                     unsigned long long* counters, unsigned long long* fb_list)
 {
     __shared__ PriorTab PT;
@@ -278,19 +277,17 @@ __global__ __launch_bounds__(BLOCK) void k_rate_mlp(GridView g, SpeciesView ion,
     load_net(m.params, lane, net);
     __syncthreads();
     for (int sc = blockIdx.x; sc < g.nsc; sc += gridDim.x) {
-        const int n = ion.count[sc];
-        const int64_t base = (int64_t)sc * ion.cap;
-        const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
+        const int n = pb.count[sc];
+        const int64_t base = (int64_t)sc * pb.cap;
         for (int t = 64 * wave + lane; t - lane < n; t += BLOCK) {
             float x0 = 0.f, x1 = 0.f, prior = 0.f;
-            int Z = 0, zin = -1;
+            int zin = -1;
             bool act = false, inr = false;
             const int64_t p = base + t;
             if (t < n) {
-                Z = ion.zs[p];
-                act = Z < tab.z_max;
-                const int64_t gi = (int64_t)(scx * SX + (int)ion.x[p]) +
-                                   (int64_t)g.nx * ((scy * SY + (int)ion.y[p]) + (int64_t)g.ny * (scz * SZ + (int)ion.z[p]));
+                const int pr = pb.list[p], Z = pr >> 8;
+                act = true;
+                const int64_t gi = cell_index(g, sc, pr & 255);
                 const float fkT = (float)kT[gi], fne = (float)ne[gi];
                 inr = act && Z < 6 && fkT >= m.t_min && fkT <= m.t_max && fne >= m.n_min && fne <= m.n_max;
                 if (inr) {
@@ -312,16 +309,16 @@ __global__ __launch_bounds__(BLOCK) void k_rate_mlp(GridView g, SpeciesView ion,
                         (unsigned long long)p;
             }
             if (t < n) {
-                // ln nu <= ~40 on the trained range; fallback ions are written by the second kernel
-                nu[p] = inr ? (double)__expf(prior + m.mu + m.s * y) : 0.0;
+                // ln nu <= ~40 on the trained range; fallback pairs are written by the second kernel
+                pb.nu[p] = inr ? (double)__expf(prior + m.mu + m.s * y) : 0.0;
             }
         }
     }
 }
 
-// The exact FP64 rate for the ions listed by k_rate_mlp.
-__global__ __launch_bounds__(BLOCK) void k_rate_fallback(GridView g, SpeciesView ion, IonTables tab, const double* ne,
-                                                         const double* kT, double* nu, const double* gl,
+// The exact FP64 rate for the pairs listed by the rate kernels, sign bit set.
+__global__ __launch_bounds__(BLOCK) void k_rate_fallback(GridView g, PairBuffers pb, IonTables tab, const double* ne,
+                                                         const double* kT, const double* gl,
                                                          const unsigned long long* fb_list,
                                                          const unsigned long long* counters)
 {
@@ -332,37 +329,34 @@ __global__ __launch_bounds__(BLOCK) void k_rate_fallback(GridView g, SpeciesView
     for (unsigned long long i = (unsigned long long)blockIdx.x * BLOCK + threadIdx.x; i < cnt;
          i += (unsigned long long)gridDim.x * BLOCK) {
         const int64_t p = (int64_t)fb_list[i];
-        const int sc = (int)(p / ion.cap);
-        const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
-        const int64_t gi = (int64_t)(scx * SX + (int)ion.x[p]) +
-                           (int64_t)g.nx * ((scy * SY + (int)ion.y[p]) + (int64_t)g.ny * (scz * SZ + (int)ion.z[p]));
-        const int Z = ion.zs[p];
-        nu[p] = rate_exact(kT[gi], ne[gi], tab, Z, glx, glw);
+        const int pr = pb.list[p];
+        const int64_t gi = cell_index(g, (int)(p / pb.cap), pr & 255);
+        pb.nu[p] = -rate_exact(kT[gi], ne[gi], tab, pr >> 8, glx, glw);
     }
 }
 
-hipError_t launch_rate_mlp(const GridView& g, const SpeciesView& ion, const IonTables& tab, const MlpLaunch& ml,
-                           const double* ne, const double* kT, double* nu, const double* gl,
-                           unsigned long long* counters, unsigned long long* fb_list, hipStream_t st)
+hipError_t launch_rate_mlp(const GridView& g, const PairBuffers& pb, const IonTables& tab, const MlpLaunch& ml,
+                           const double* ne, const double* kT, const double* gl, unsigned long long* counters,
+                           unsigned long long* fb_list, hipStream_t st)
 {
     MlpArgs m{ml.params, (float)ml.mu, (float)ml.s, (float)ml.t_min, (float)ml.t_max, (float)ml.n_min, (float)ml.n_max};
     const int blocks = g.nsc < 1024 ? g.nsc : 1024;
     if (ml.act == PIC_MLP_RELU)
-        hipLaunchKernelGGL(k_rate_mlp<PIC_MLP_RELU>, dim3(blocks), dim3(BLOCK), 0, st, g, ion, tab, m, ne, kT, nu,
-                           counters, fb_list);
+        hipLaunchKernelGGL(k_rate_mlp<PIC_MLP_RELU>, dim3(blocks), dim3(BLOCK), 0, st, g, pb, tab, m, ne, kT, counters,
+                           fb_list);
     else
-        hipLaunchKernelGGL(k_rate_mlp<PIC_MLP_SILU>, dim3(blocks), dim3(BLOCK), 0, st, g, ion, tab, m, ne, kT, nu,
-                           counters, fb_list);
+        hipLaunchKernelGGL(k_rate_mlp<PIC_MLP_SILU>, dim3(blocks), dim3(BLOCK), 0, st, g, pb, tab, m, ne, kT, counters,
+                           fb_list);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_rate_fallback(g, ion, tab, ne, kT, nu, gl, fb_list, counters, st);
+    return launch_rate_fallback(g, pb, tab, ne, kT, gl, fb_list, counters, st);
 }
 
-hipError_t launch_rate_fallback(const GridView& g, const SpeciesView& ion, const IonTables& tab, const double* ne,
-                                const double* kT, double* nu, const double* gl, const unsigned long long* fb_list,
+hipError_t launch_rate_fallback(const GridView& g, const PairBuffers& pb, const IonTables& tab, const double* ne,
+                                const double* kT, const double* gl, const unsigned long long* fb_list,
                                 const unsigned long long* counters, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_rate_fallback, dim3(256), dim3(BLOCK), 0, st, g, ion, tab, ne, kT, nu, gl, fb_list, counters);
+    hipLaunchKernelGGL(k_rate_fallback, dim3(256), dim3(BLOCK), 0, st, g, pb, tab, ne, kT, gl, fb_list, counters);
     return hipGetLastError();
 }
 

@@ -6,7 +6,7 @@
 // factor e^{-P_Z/kT} and the vbar / kT prefactor stay analytic, so the table
 // holds a slowly varying function; outside [RATE_TABLE_TMIN, RATE_TABLE_TMAX]
 // the exact quadrature is used.
-#include "ionize_internal.hpp"
+#include "ionize_step.hpp"
 
 namespace pic {
 
@@ -67,35 +67,31 @@ __device__ inline bool rate_from_table(double kT, double ne, const IonTables& ta
     return true;
 }
 
-// One thread per ion slot: blockIdx.x the supercell, blockIdx.y the chunk of
-// BLOCK slots (many short blocks keep enough loads in flight).  Ions whose
+// One thread per (cell, Z) pair: blockIdx.x the supercell, blockIdx.y the chunk
+// of BLOCK pairs (many short blocks keep enough loads in flight).  Pairs whose
 // cell lies outside the table's kT range are appended to fb_list (their
 // count in counters[CNT_FALLBACK]) and take the exact quadrature in the fallback kernel.
-__global__ __launch_bounds__(BLOCK) void k_rate_table(GridView g, SpeciesView ion, IonTables tab, const double* ne,
-                                                      const double* kT, double* nu, const double* table,
+__global__ __launch_bounds__(BLOCK) void k_rate_table(GridView g, PairBuffers pb, IonTables tab, const double* ne,
+                                                      const double* kT, const double* table,
                                                       unsigned long long* counters, unsigned long long* fb_list)
 {
     const int sc = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int n = ion.count[sc];
+    const int n = pb.count[sc];
     const int t0 = blockIdx.y * BLOCK;
     if (t0 >= n) return;  // block-uniform
-    const int64_t base = (int64_t)sc * ion.cap;
-    const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
+    const int64_t base = (int64_t)sc * pb.cap;
     {
         const int t = t0 + tid;
         const int64_t p = base + t;
         bool fb = false;
         if (t < n) {
-            const int Z = ion.zs[p];
+            const int pr = pb.list[p];
             double v = 0.0;
-            if (Z < tab.z_max) {
-                const int64_t gi = (int64_t)(scx * SX + (int)ion.x[p]) +
-                                   (int64_t)g.nx * ((scy * SY + (int)ion.y[p]) + (int64_t)g.ny * (scz * SZ + (int)ion.z[p]));
-                const double t_ev = kT[gi], n_cm3 = ne[gi];
-                fb = !rate_from_table(t_ev, n_cm3, tab, Z, table, v) && t_ev > 0.0 && n_cm3 > 0.0;
-            }
-            nu[p] = v;
+            const int64_t gi = cell_index(g, sc, pr & 255);
+            const double t_ev = kT[gi], n_cm3 = ne[gi];
+            fb = !rate_from_table(t_ev, n_cm3, tab, pr >> 8, table, v) && t_ev > 0.0 && n_cm3 > 0.0;
+            pb.nu[p] = v;
         }
         const unsigned long long fmask = __ballot(fb);
         if (fmask) {  // rare
@@ -111,15 +107,15 @@ __global__ __launch_bounds__(BLOCK) void k_rate_table(GridView g, SpeciesView io
     }
 }
 
-hipError_t launch_rate_table(const GridView& g, const SpeciesView& ion, const IonTables& tab, const double* ne,
-                             const double* kT, double* nu, const double* table, const double* gl,
+hipError_t launch_rate_table(const GridView& g, const PairBuffers& pb, const IonTables& tab, const double* ne,
+                             const double* kT, const double* table, const double* gl,
                              unsigned long long* counters, unsigned long long* fb_list, hipStream_t st)
 {
-    const dim3 grid(g.nsc, (ion.cap + BLOCK - 1) / BLOCK);
-    hipLaunchKernelGGL(k_rate_table, grid, dim3(BLOCK), 0, st, g, ion, tab, ne, kT, nu, table, counters, fb_list);
+    const dim3 grid(g.nsc, (pb.cap + BLOCK - 1) / BLOCK);
+    hipLaunchKernelGGL(k_rate_table, grid, dim3(BLOCK), 0, st, g, pb, tab, ne, kT, table, counters, fb_list);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_rate_fallback(g, ion, tab, ne, kT, nu, gl, fb_list, counters, st);
+    return launch_rate_fallback(g, pb, tab, ne, kT, gl, fb_list, counters, st);
 }
 
 // ln nu of independent samples from the table (exact outside its range).

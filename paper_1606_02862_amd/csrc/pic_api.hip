@@ -49,10 +49,10 @@ struct pic_ctx {
     double* mom4 = nullptr;                  // per-cell sum w and mean u (energy loss)
     double* de = nullptr;                    // per-cell ionisation energy to pay (energy loss)
     int32_t* old_count = nullptr;            // per-supercell electron count before the appends
-    double* nu[PIC_MAX_SPECIES] = {};        // per ion slot rate (1/s)
+    PairBuffers pairs[PIC_MAX_SPECIES] = {}; // the (cell, Z) pairs of a step and their rates
     double* rtab[PIC_MAX_SPECIES] = {};      // tabulated subshell sums (PIC_RATE_TABLE), built at first use
     bool rtab_ready[PIC_MAX_SPECIES] = {};
-    unsigned long long* fbl[PIC_MAX_SPECIES] = {};  // per ion slot: surrogate fallback list
+    unsigned long long* fbl[PIC_MAX_SPECIES] = {};  // per pair: rate fallback list
     unsigned long long* counters = nullptr;  // CNT_WORDS ionisation counters (fallback list, striped active / ionised)
     hipEvent_t iev[4] = {};
     // surrogate per ion species
@@ -308,9 +308,15 @@ int alloc_ionisation(pic_ctx* c)
         return fail(c, PIC_ERR_OOM, "device allocation of ionisation buffers failed");
     for (int s = 0; s < c->nsp; ++s) {
         if (c->sp[s].desc.z_max == 0) continue;
-        if (!(c->nu[s] = (double*)dev_alloc(c, (size_t)c->g.nsc * c->sp[s].v.cap * 8)) ||
+        PairBuffers& pb = c->pairs[s];
+        pb.cap = SC_CELLS * c->sp[s].desc.z_max;
+        const size_t npair = (size_t)c->g.nsc * pb.cap;
+        if (!(pb.nu = (double*)dev_alloc(c, npair * 8)) || !(pb.list = (uint16_t*)dev_alloc(c, npair * 2)) ||
+            !(pb.info = (uint32_t*)dev_alloc(c, (size_t)N * 4)) ||
+            !(pb.count = (int32_t*)dev_alloc(c, (size_t)c->g.nsc * 4)) ||
+            !(pb.cell = (uint8_t*)dev_alloc(c, (size_t)c->g.nsc * c->sp[s].v.cap)) ||
             !(c->rtab[s] = (double*)dev_alloc(c, (size_t)PIC_MAX_ZSTATES * RATE_TABLE_N * 8)) ||
-            !(c->fbl[s] = (unsigned long long*)dev_alloc(c, (size_t)c->g.nsc * c->sp[s].v.cap * 8)))
+            !(c->fbl[s] = (unsigned long long*)dev_alloc(c, npair * 8)))
             return fail(c, PIC_ERR_OOM, "device allocation of ionisation rates failed");
         pic_ctx::Mlp& m = c->mlp[s];
         if (!(m.params = (float*)dev_alloc(c, PIC_MLP_NPARAM * 4)) || !(m.m = (float*)dev_alloc(c, PIC_MLP_NPARAM * 4)) ||
@@ -1097,18 +1103,20 @@ int ionize_impl(pic_ctx* c, pic_rate_mode_t mode, bool staged, pic_ionize_stats_
             HIPCHK(c, launch_ionize_exact(c->g, c->sp[s].v, c->sp[e].v, tab, a, db, nrdv, c->ne, c->kT,
                                           eloss ? c->mom4 : nullptr, c->counters, c->stream));
         } else {
-            HIPCHK(c, launch_moments(c->g, c->sp[e].v, nrdv, c->ne, c->kT, eloss ? c->mom4 : nullptr, c->stream));
+            const PairBuffers& pb = c->pairs[s];
+            HIPCHK(c, launch_moments_pairs(c->g, c->sp[e].v, c->sp[s].v, tab.z_max, pb, nrdv, c->ne, c->kT,
+                                           eloss ? c->mom4 : nullptr, c->stream));
             HIPCHK(c, hipEventRecord(c->iev[1], c->stream));
             if (mode == PIC_RATE_EXACT)
-                HIPCHK(c, launch_rate_exact(c->g, c->sp[s].v, tab, c->ne, c->kT, c->nu[s], c->gl, c->stream));
+                HIPCHK(c, launch_rate_exact(c->g, pb, tab, c->ne, c->kT, c->gl, c->stream));
             else if (mode == PIC_RATE_TABLE)
-                HIPCHK(c, launch_rate_table(c->g, c->sp[s].v, tab, c->ne, c->kT, c->nu[s], c->rtab[s], c->gl,
-                                            c->counters, c->fbl[s], c->stream));
+                HIPCHK(c, launch_rate_table(c->g, pb, tab, c->ne, c->kT, c->rtab[s], c->gl, c->counters, c->fbl[s],
+                                            c->stream));
             else
-                HIPCHK(c, launch_rate_mlp(c->g, c->sp[s].v, tab, mlp_launch(c, s), c->ne, c->kT, c->nu[s], c->gl,
-                                          c->counters, c->fbl[s], c->stream));
+                HIPCHK(c, launch_rate_mlp(c->g, pb, tab, mlp_launch(c, s), c->ne, c->kT, c->gl, c->counters,
+                                          c->fbl[s], c->stream));
             HIPCHK(c, hipEventRecord(c->iev[2], c->stream));
-            HIPCHK(c, launch_draw_append(c->g, c->sp[s].v, c->sp[e].v, tab, a, c->nu[s], db, c->counters, c->stream));
+            HIPCHK(c, launch_draw_append(c->g, c->sp[s].v, c->sp[e].v, tab, a, pb, db, c->counters, c->stream));
         }
         if (eloss) HIPCHK(c, launch_energy_loss(c->g, c->sp[e].v, db, c->stream));
         HIPCHK(c, hipEventRecord(c->iev[3], c->stream));
@@ -1123,8 +1131,8 @@ int ionize_impl(pic_ctx* c, pic_rate_mode_t mode, bool staged, pic_ionize_stats_
         for (int k = 0; k < CNT_STRIPES; ++k) {
             st.ions_active += (int64_t)cnt[CNT_ACTIVE + k];
             st.ionized += (int64_t)cnt[CNT_FIRED + k];
+            st.fallback += (int64_t)cnt[CNT_FBIONS + k];
         }
-        st.fallback += (int64_t)cnt[CNT_FALLBACK];
         std::vector<int32_t> cc;
         st.electrons = host_count(c, e, cc);
         c->sp[e].wmax = std::max(c->sp[e].wmax, c->sp[s].wmax);  // born electrons carry ion weights
