@@ -5,6 +5,7 @@
 #pragma once
 
 #include "pic_device.hpp"
+#include "rate_log.hpp"
 
 namespace pic {
 
@@ -63,7 +64,7 @@ struct DrawArgs {
 struct DrawBuffers {
     const double* ne;           // per cell n_e (cm^-3)
     const double* kT;           // per cell kT_e (eV)
-    const double* gl;           // Gauss-Laguerre rule (later events' exact rates)
+    const double* gl;           // Gauss-Laguerre rule and logarithm table (exact rates)
     const double* mom4;         // per cell N = sum w and mean u (energy loss), or nullptr
     double* de;                 // per cell sum of w * P over the events (energy loss), or nullptr
     int32_t* old_count;         // per supercell electron count before the appends (energy loss), or nullptr
@@ -166,61 +167,63 @@ unsigned char* noalloc_scratch(int device);
 NoallocStaging noalloc_staging(unsigned char* base);
 
 // ---------------------------------------------------------------- Lotz rate
+// What the quadrature reads, in LDS: the rule and the logarithm's table.
+struct GlRule {
+    double x[GL_NODES], w[GL_NODES];
+    double2 lt[LOG_N];
+};
+constexpr int GL_WORDS = 2 * GL_NODES + 2 * LOG_N;  // doubles of the device copy, in the same order
+static_assert(sizeof(GlRule) == GL_WORDS * sizeof(double), "GlRule is the device copy's layout");
+
+// Copies the rule to LDS; a barrier is the caller's.
+__device__ inline void load_rule(const double* gl, GlRule& rule)
+{
+    double* d = reinterpret_cast<double*>(&rule);
+    for (int t = threadIdx.x; t < GL_WORDS; t += blockDim.x) d[t] = gl[t];
+}
+
 // One subshell (p, a, b, c, q) with E = p + kT x:
 //   <sigma v>_j = vbar (a q / (p kT)) e^{-p/kT} sum_k w_k ln(1 + x_k r) (1 - b e^{-c x_k r}),  r = kT / p,
-// FP64; the exponential only where b != 0.
-__device__ inline double lotz_sum(double r, double b, double c, const double* glx, const double* glw)
+// FP64; the exponential only where b != 0.  The nodes k0, k0 + STEP, ... of the sum.
+template <int STEP>
+__device__ inline double lotz_sum(double r, double b, double c, const GlRule& rule, int k0)
 {
     double s = 0.0;
-    if (b == 0.0) {
+    if (!(rule.x[GL_NODES - 1] * r <= LOG_Y_MAX)) {  // past log1p_pos
+        for (int k = k0; k < GL_NODES; k += STEP) {
+            const double xr = rule.x[k] * r;
+            s = fma(rule.w[k] * log1p(xr), b == 0.0 ? 1.0 : 1.0 - b * exp(-c * xr), s);
+        }
+    } else if (b == 0.0) {
 #pragma unroll 8
-        for (int k = 0; k < GL_NODES; ++k) s = fma(glw[k], log1p(glx[k] * r), s);
+        for (int k = k0; k < GL_NODES; k += STEP) s = fma(rule.w[k], log1p_pos(rule.x[k] * r, rule.lt), s);
     } else {
 #pragma unroll 4
-        for (int k = 0; k < GL_NODES; ++k) {
-            const double xr = glx[k] * r;
-            s = fma(glw[k] * log1p(xr), 1.0 - b * exp(-c * xr), s);
+        for (int k = k0; k < GL_NODES; k += STEP) {
+            const double xr = rule.x[k] * r;
+            s = fma(rule.w[k] * log1p_pos(xr, rule.lt), 1.0 - b * exp(-c * xr), s);
         }
     }
     return s;
 }
 
 // sum_j (a_j q_j / p_j) e^{-(p_j - P)/kT} S_j over the subshells of state Z, P = P[Z]:
-// the state's <sigma v> is vbar / kT e^{-P/kT} times this.
-__device__ inline double lotz_shells(double kT, const IonTables& t, int Z, const double* glx, const double* glw)
+// the state's <sigma v> is vbar / kT e^{-P/kT} times this.  LANES = 4: a group
+// of four consecutive lanes with the same kT and Z, lane j of the group taking
+// the nodes j, j + 4, ...; the four partial sums are added so that every lane
+// returns the same total.
+template <int LANES = 1>
+__device__ inline double lotz_shells(double kT, const IonTables& t, int Z, const GlRule& rule)
 {
+    static_assert(LANES == 1 || LANES == 4, "one lane or a group of four");
     double acc = 0.0;
     for (int j = 0; j < t.ns[Z]; ++j) {
         const double p = t.sp[Z][j];
-        double v = t.aq[Z][j] / p * lotz_sum(kT / p, t.sb[Z][j], t.sc[Z][j], glx, glw);
-        if (j > 0) v *= exp(-(p - t.P[Z]) / kT);
-        acc += v;
-    }
-    return acc;
-}
-
-// lotz_shells by a group of four consecutive lanes that hold the same kT and Z:
-// lane j of the group takes the nodes j, j + 4, ..., and the four partial sums
-// are added so that every lane returns the same total.
-__device__ inline double lotz_shells4(double kT, const IonTables& t, int Z, const double* glx, const double* glw)
-{
-    const int j4 = threadIdx.x & 3;
-    double acc = 0.0;
-    for (int j = 0; j < t.ns[Z]; ++j) {
-        const double p = t.sp[Z][j], r = kT / p, b = t.sb[Z][j], c = t.sc[Z][j];
-        double s = 0.0;
-        if (b == 0.0) {
-#pragma unroll 8
-            for (int k = j4; k < GL_NODES; k += 4) s = fma(glw[k], log1p(glx[k] * r), s);
-        } else {
-#pragma unroll 4
-            for (int k = j4; k < GL_NODES; k += 4) {
-                const double xr = glx[k] * r;
-                s = fma(glw[k] * log1p(xr), 1.0 - b * exp(-c * xr), s);
-            }
+        double s = lotz_sum<LANES>(kT / p, t.sb[Z][j], t.sc[Z][j], rule, LANES == 4 ? (int)(threadIdx.x & 3) : 0);
+        if constexpr (LANES == 4) {
+            s += __shfl_xor(s, 1, 64);
+            s += __shfl_xor(s, 2, 64);
         }
-        s += __shfl_xor(s, 1, 64);
-        s += __shfl_xor(s, 2, 64);
         double v = t.aq[Z][j] / p * s;
         if (j > 0) v *= exp(-(p - t.P[Z]) / kT);
         acc += v;
@@ -230,26 +233,17 @@ __device__ inline double lotz_shells4(double kT, const IonTables& t, int Z, cons
 
 __device__ inline double vbar_cm_s(double kT) { return C_CM_S * sqrt(8.0 * kT / (M_PI * ME_C2_EV)); }
 
-__device__ inline double rate_exact(double kT, double ne, const IonTables& t, int Z, const double* glx,
-                                    const double* glw)
+template <int LANES = 1>
+__device__ inline double rate_exact(double kT, double ne, const IonTables& t, int Z, const GlRule& rule)
 {
     if (!(kT > 0.0) || !(ne > 0.0)) return 0.0;
-    return ne * vbar_cm_s(kT) / kT * exp(-t.P[Z] / kT) * lotz_shells(kT, t, Z, glx, glw);
+    return ne * vbar_cm_s(kT) / kT * exp(-t.P[Z] / kT) * lotz_shells<LANES>(kT, t, Z, rule);
 }
 
-// rate_exact by a group of four lanes (lotz_shells4)
-__device__ inline double rate_exact4(double kT, double ne, const IonTables& t, int Z, const double* glx,
-                                     const double* glw)
-{
-    if (!(kT > 0.0) || !(ne > 0.0)) return 0.0;
-    return ne * vbar_cm_s(kT) / kT * exp(-t.P[Z] / kT) * lotz_shells4(kT, t, Z, glx, glw);
-}
-
-__device__ inline double ln_rate_exact(double kT, double ne, const IonTables& t, int Z, const double* glx,
-                                       const double* glw)
+__device__ inline double ln_rate_exact(double kT, double ne, const IonTables& t, int Z, const GlRule& rule)
 {
     if (!(kT > 0.0) || !(ne > 0.0)) return -INFINITY;
-    return log(ne * vbar_cm_s(kT) / kT) - t.P[Z] / kT + log(lotz_shells(kT, t, Z, glx, glw));
+    return log(ne * vbar_cm_s(kT) / kT) - t.P[Z] / kT + log(lotz_shells(kT, t, Z, rule));
 }
 
 }  // namespace pic

@@ -151,7 +151,7 @@ __device__ inline uint64_t word(const Philox4& r, int e)
 // and of (id, species, 6, step) after; later events take the exact rate.
 template <bool CHAIN>
 __device__ inline int ion_events(const IonTables& tab, const DrawArgs& a, uint32_t id, int Z0, double nu0, double kT,
-                                 double ne, const double* glx, const double* glw)
+                                 double ne, const GlRule& rule)
 {
     const Philox4 r = philox4x64_10((uint64_t)id, (uint64_t)a.species_index, PURPOSE_IONIZE, (uint64_t)a.step, a.seed, 0);
     if constexpr (!CHAIN) return u01(r.v[0]) < -expm1(-nu0 * a.dt_phys) ? 1 : 0;
@@ -159,7 +159,7 @@ __device__ inline int ion_events(const IonTables& tab, const DrawArgs& a, uint32
     double t = 0.0;
     int nev = 0;
     for (int e = 0; e < a.max_events && Z0 + e < tab.z_max; ++e) {
-        const double rate = e == 0 ? nu0 : rate_exact(kT, ne, tab, Z0 + e, glx, glw);
+        const double rate = e == 0 ? nu0 : rate_exact(kT, ne, tab, Z0 + e, rule);
         if (!(rate > 0.0)) break;
         if (e == 4)
             r2 = philox4x64_10((uint64_t)id, (uint64_t)a.species_index, PURPOSE_IONIZE_MORE, (uint64_t)a.step, a.seed, 0);

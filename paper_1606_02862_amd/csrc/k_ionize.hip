@@ -62,17 +62,17 @@ hipError_t launch_moments_pairs(const GridView& g, const SpeciesView& e, const S
 __global__ __launch_bounds__(BLOCK) void k_rate_exact(GridView g, PairBuffers pb, IonTables tab, const double* ne,
                                                       const double* kT, const double* gl)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
+    __shared__ GlRule rule;
     const int sc = blockIdx.x;
     const int tid = threadIdx.x;
-    if (tid < GL_NODES) { glx[tid] = gl[tid]; glw[tid] = gl[GL_NODES + tid]; }
+    load_rule(gl, rule);
     __syncthreads();
     const int n = pb.count[sc];
     const int64_t base = (int64_t)sc * pb.cap;
     for (int i = tid >> 2; i < n; i += BLOCK / 4) {
         const int pr = pb.list[base + i];
         const int64_t gi = cell_index(g, sc, pr & 255);
-        const double v = rate_exact4(kT[gi], ne[gi], tab, pr >> 8, glx, glw);
+        const double v = rate_exact<4>(kT[gi], ne[gi], tab, pr >> 8, rule);
         if ((tid & 3) == 0) pb.nu[base + i] = v;
     }
 }
@@ -89,13 +89,13 @@ __global__ __launch_bounds__(BLOCK) void k_ln_rate_exact(int64_t n, const double
                                                          const int32_t* Z, IonTables tab, const double* gl,
                                                          double* out)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
-    if (threadIdx.x < GL_NODES) { glx[threadIdx.x] = gl[threadIdx.x]; glw[threadIdx.x] = gl[GL_NODES + threadIdx.x]; }
+    __shared__ GlRule rule;
+    load_rule(gl, rule);
     __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     if (i >= n) return;
     const int z = Z[i];
-    out[i] = (z >= 0 && z < tab.z_max) ? ln_rate_exact(kT[i], ne[i], tab, z, glx, glw) : -INFINITY;
+    out[i] = (z >= 0 && z < tab.z_max) ? ln_rate_exact(kT[i], ne[i], tab, z, rule) : -INFINITY;
 }
 
 hipError_t launch_ln_rate_exact(int64_t n, const double* kT, const double* ne, const int32_t* Z, const IonTables& tab,
@@ -120,12 +120,12 @@ __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView i
                                                        DrawArgs a, PairBuffers pb, DrawBuffers db,
                                                        unsigned long long* counters)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
+    __shared__ GlRule rule;
     __shared__ DrawLds s_d;
     __shared__ uint32_t s_info[SC_CELLS];  // the cells' pairs
     const int sc = blockIdx.x;
     const int tid = threadIdx.x;
-    if (CHAIN && tid < GL_NODES) { glx[tid] = db.gl[tid]; glw[tid] = db.gl[GL_NODES + tid]; }
+    if (CHAIN) load_rule(db.gl, rule);
     if (tid == 0) s_d = DrawLds{0, 0, 0, 0};
     s_info[tid] = pb.info[(int64_t)sc * SC_CELLS + tid];
     __syncthreads();
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView i
                 // the ion's cell, for later events' rates and the energy account only
                 if (CHAIN || a.energy_loss) gi = cell_index(g, sc, cells[k]);
                 nev = ion_events<CHAIN>(tab, a, ids[k], Z0, fabs(nus[k]), CHAIN ? db.kT[gi] : 0.0,
-                                        CHAIN ? db.ne[gi] : 0.0, glx, glw);
+                                        CHAIN ? db.ne[gi] : 0.0, rule);
             }
             const int b = wave_reserve<CHAIN>(nev, &s_d.add);  // every lane of the wave
             if (nev) fired += append_events(ion, el, tab, a, db.de, sc, p, gi, ids[k], Z0, nev, b, ebase, room, full);
@@ -216,11 +216,11 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
     __shared__ PairLds pl;
     __shared__ uint16_t s_list[SC_CELLS * PIC_MAX_ZSTATES];
     __shared__ double s_nu[SC_CELLS * PIC_MAX_ZSTATES];
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
+    __shared__ GlRule rule;
     __shared__ DrawLds s_d;
     const int sc = blockIdx.x;
     const int tid = threadIdx.x;
-    if (tid < GL_NODES) { glx[tid] = db.gl[tid]; glw[tid] = db.gl[GL_NODES + tid]; }
+    load_rule(db.gl, rule);
     if (tid == 0) s_d = DrawLds{0, 0, 0, 0};
     moments_accumulate(el, sc, mom);  // its barriers also publish the rule and the reset above
     {
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
                                [&](int i, int c, int Z) { s_list[i] = (uint16_t)(c | Z << 8); });
     for (int i = tid >> 2; i < np; i += BLOCK / 4) {
         const int pr = s_list[i], c = pr & 255;
-        const double v = rate_exact4(mom.acc[1][c], mom.acc[0][c], tab, pr >> 8, glx, glw);
+        const double v = rate_exact<4>(mom.acc[1][c], mom.acc[0][c], tab, pr >> 8, rule);
         if ((tid & 3) == 0) s_nu[i] = v;
     }
     __syncthreads();
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
             const double cne = mom.acc[0][cell], ckT = mom.acc[1][cell];
             const double nu0 = s_nu[pl.off[cell] + __popc(pl.mask[cell] & ((1u << Z) - 1u))];
             id = ion.id[p];
-            nev = ion_events<CHAIN>(tab, a, id, Z, nu0, ckT, cne, glx, glw);
+            nev = ion_events<CHAIN>(tab, a, id, Z, nu0, ckT, cne, rule);
         }
         const int b = wave_reserve<CHAIN>(nev, &s_d.add);
         if (nev) {

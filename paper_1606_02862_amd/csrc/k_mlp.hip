@@ -246,10 +246,9 @@ template <int ACT> __device__ inline float forward64(const Net& n, int lane, flo
 // Exact FP64 rate for the (rare) samples outside the trained range, kept out
 // of line so that its register footprint does not lower the occupancy of the
 // surrogate path.
-__device__ __noinline__ double fallback_rate(double kT, double ne, const IonTables& tab, int Z, const double* glx,
-                                            const double* glw)
+__device__ __noinline__ double fallback_rate(double kT, double ne, const IonTables& tab, int Z, const GlRule& rule)
 {
-    return rate_exact(kT, ne, tab, Z, glx, glw);
+    return rate_exact(kT, ne, tab, Z, rule);
 }
 
 struct MlpArgs {
@@ -322,8 +321,8 @@ __global__ __launch_bounds__(BLOCK) void k_rate_fallback(GridView g, PairBuffers
                                                          const unsigned long long* fb_list,
                                                          const unsigned long long* counters)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
-    if (threadIdx.x < GL_NODES) { glx[threadIdx.x] = gl[threadIdx.x]; glw[threadIdx.x] = gl[GL_NODES + threadIdx.x]; }
+    __shared__ GlRule rule;
+    load_rule(gl, rule);
     __syncthreads();
     const unsigned long long cnt = counters[CNT_FALLBACK];
     for (unsigned long long i = (unsigned long long)blockIdx.x * BLOCK + threadIdx.x; i < cnt;
@@ -331,7 +330,7 @@ __global__ __launch_bounds__(BLOCK) void k_rate_fallback(GridView g, PairBuffers
         const int64_t p = (int64_t)fb_list[i];
         const int pr = pb.list[p];
         const int64_t gi = cell_index(g, (int)(p / pb.cap), pr & 255);
-        pb.nu[p] = -rate_exact(kT[gi], ne[gi], tab, pr >> 8, glx, glw);
+        pb.nu[p] = -rate_exact(kT[gi], ne[gi], tab, pr >> 8, rule);
     }
 }
 
@@ -365,11 +364,11 @@ template <int ACT>
 __global__ __launch_bounds__(BLOCK) void k_ln_rate_mlp(int64_t n, const double* kT, const double* ne, const int32_t* Zs,
                                                        IonTables tab, MlpArgs m, const double* gl, double* out)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
+    __shared__ GlRule rule;
     __shared__ PriorTab PT;
     __shared__ IonTables s_tab;  // the out-of-line fallback reads the tables from LDS
     const int tid = threadIdx.x, lane = tid & 63;
-    if (tid < GL_NODES) { glx[tid] = gl[tid]; glw[tid] = gl[GL_NODES + tid]; }
+    load_rule(gl, rule);
     if (tid == 0) s_tab = tab;
     fill_prior(tab, PT);
     Net net;
@@ -395,7 +394,7 @@ __global__ __launch_bounds__(BLOCK) void k_ln_rate_mlp(int64_t n, const double* 
             if (inr) {
                 out[i] = (double)(prior + m.mu + m.s * y);
             } else if (Z >= 0 && Z < tab.z_max) {
-                const double v = fallback_rate(kT[i], ne[i], s_tab, Z, glx, glw);
+                const double v = fallback_rate(kT[i], ne[i], s_tab, Z, rule);
                 out[i] = v > 0.0 ? log(v) : -INFINITY;
             } else {
                 out[i] = -INFINITY;
@@ -427,8 +426,8 @@ hipError_t launch_ln_rate_mlp(int64_t n, const double* kT, const double* ne, con
 __global__ __launch_bounds__(BLOCK) void k_mlp_gen(int64_t n, uint64_t seed, MlpGen a, IonTables tab, const double* gl,
                                                    float* X, double* r)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
-    if (threadIdx.x < GL_NODES) { glx[threadIdx.x] = gl[threadIdx.x]; glw[threadIdx.x] = gl[GL_NODES + threadIdx.x]; }
+    __shared__ GlRule rule;
+    load_rule(gl, rule);
     __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     if (i >= n) return;
@@ -445,7 +444,7 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_gen(int64_t n, uint64_t seed, Mlp
     const double P = tab.P[Z], aq = tab.aq[Z][0];
     const double z = P / kT;
     const double prior = log(ne * vbar_cm_s(kT) * aq / (P * kT)) - z + log(log1p(1.0 / z));
-    r[i] = ln_rate_exact(kT, ne, tab, Z, glx, glw) - prior;
+    r[i] = ln_rate_exact(kT, ne, tab, Z, rule) - prior;
 }
 
 hipError_t launch_mlp_gen(int64_t n, uint64_t seed, const MlpGen& a, const IonTables& tab, const double* gl, float* X,

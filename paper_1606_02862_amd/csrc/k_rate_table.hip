@@ -21,14 +21,14 @@ __host__ __device__ inline double rate_table_s0() { return log(RATE_TABLE_TMIN) 
 
 __global__ __launch_bounds__(BLOCK) void k_rate_table_build(IonTables tab, const double* gl, double* out)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
-    if (threadIdx.x < GL_NODES) { glx[threadIdx.x] = gl[threadIdx.x]; glw[threadIdx.x] = gl[GL_NODES + threadIdx.x]; }
+    __shared__ GlRule rule;
+    load_rule(gl, rule);
     __syncthreads();
     const int i = blockIdx.x * BLOCK + threadIdx.x;
     if (i >= tab.z_max * RATE_TABLE_N) return;
     const int z = i / RATE_TABLE_N, k = i % RATE_TABLE_N;
     const double kT = exp(rate_table_s0() + k * rate_table_ds());
-    out[i] = log(lotz_shells(kT, tab, z, glx, glw));
+    out[i] = log(lotz_shells(kT, tab, z, rule));
 }
 
 hipError_t launch_rate_table_build(const IonTables& tab, const double* gl, double* table, hipStream_t st)
@@ -123,8 +123,8 @@ __global__ __launch_bounds__(BLOCK) void k_ln_rate_table(int64_t n, const double
                                                          const int32_t* Z, IonTables tab, const double* table,
                                                          const double* gl, double* out)
 {
-    __shared__ double glx[GL_NODES], glw[GL_NODES];
-    if (threadIdx.x < GL_NODES) { glx[threadIdx.x] = gl[threadIdx.x]; glw[threadIdx.x] = gl[GL_NODES + threadIdx.x]; }
+    __shared__ GlRule rule;
+    load_rule(gl, rule);
     __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     if (i >= n) return;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(BLOCK) void k_ln_rate_table(int64_t n, const double
     if (in_table(t_ev, n_cm3)) {
         out[i] = log(n_cm3 * vbar_cm_s(t_ev) / t_ev) + table_h(t_ev, z, table) - tab.P[z] / t_ev;
     } else {
-        out[i] = ln_rate_exact(t_ev, n_cm3, tab, z, glx, glw);
+        out[i] = ln_rate_exact(t_ev, n_cm3, tab, z, rule);
     }
 }
 

@@ -43,7 +43,7 @@ struct pic_ctx {
     int64_t pending_particles = 0;
     int pending_launches = 0;
     // ionisation
-    double* gl = nullptr;                    // 64 nodes then 64 weights
+    double* gl = nullptr;                    // the quadrature's nodes, weights and logarithm table (GlRule)
     double* ne = nullptr;                    // per-cell n_e (cm^-3)
     double* kT = nullptr;                    // per-cell kT_e (eV)
     double* mom4 = nullptr;                  // per-cell sum w and mean u (energy loss)
@@ -303,7 +303,7 @@ int alloc_ionisation(pic_ctx* c)
     for (int s = 0; s < c->nsp; ++s) any = any || (c->sp[s].desc.z_max > 0);
     if (!any) return PIC_OK;
     const int64_t N = (int64_t)c->grid.nx * c->grid.ny * c->grid.nz;
-    if (!(c->gl = (double*)dev_alloc(c, 2 * GL_NODES * 8)) || !(c->ne = (double*)dev_alloc(c, N * 8)) ||
+    if (!(c->gl = (double*)dev_alloc(c, GL_WORDS * 8)) || !(c->ne = (double*)dev_alloc(c, N * 8)) ||
         !(c->kT = (double*)dev_alloc(c, N * 8)) || !(c->counters = (unsigned long long*)dev_alloc(c, CNT_WORDS * 8)))
         return fail(c, PIC_ERR_OOM, "device allocation of ionisation buffers failed");
     for (int s = 0; s < c->nsp; ++s) {
@@ -333,8 +333,9 @@ int alloc_ionisation(pic_ctx* c)
     }
     const double* w;
     const double* x = gauss_laguerre_nodes(&w);
-    double rule[2 * GL_NODES];
+    double rule[GL_WORDS];
     for (int k = 0; k < GL_NODES; ++k) { rule[k] = x[k]; rule[GL_NODES + k] = w[k]; }
+    log_table(rule + 2 * GL_NODES);
     HIPCHK(c, hipMemcpyAsync(c->gl, rule, sizeof rule, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (hipEvent_t& e : c->iev) HIPCHK(c, hipEventCreate(&e));

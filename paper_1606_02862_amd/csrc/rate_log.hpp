@@ -9,7 +9,7 @@
 // the last term restoring what rounding 1 + y lost.  Interval 0 has c = 1, so a
 // small y returns ln(1 + t), t = y, with full relative accuracy; every term
 // is >= 0 otherwise and nothing cancels.  |t| < 2^-7: the Taylor series to t^8
-// leaves 2^-59 of t.  Measured against 80-bit logarithms: below 1 ulp.
+// leaves 2^-59 of t.  Measured against 80-bit logarithms: at most 1.3 ulp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,13 +21,25 @@ namespace pic {
 constexpr int LOG_N = 128;
 constexpr double LOG_Y_MAX = 1e300;  // beyond it the callers take the library log1p
 
-// {invc_i, ln c_i} of the intervals, host side (the logarithm in 80 bits)
+// {invc_i, ln c_i} of the intervals, host side.  Any invc_i near 1 / m serves, so
+// of 64 neighbouring doubles the one whose logarithm (in 80 bits) lies closest
+// to a double is taken: ln c_i then adds next to no rounding of its own where
+// it is small and the terms differ in sign.
 inline void log_table(double* t)
 {
     for (int i = 0; i < LOG_N; ++i) {
-        const double invc = i == 0 ? 1.0 : 1.0 / (1.0 + (i + 0.5) / LOG_N);
+        double invc = i == 0 ? 1.0 : 1.0 / (1.0 + (i + 0.5) / LOG_N), best = 1.0;
         t[2 * i] = invc;
-        t[2 * i + 1] = i == 0 ? 0.0 : (double)-logl((long double)invc);
+        t[2 * i + 1] = 0.0;
+        for (int k = 0; i > 0 && k < 64; ++k, invc = nextafter(invc, 0.0)) {
+            const long double l = -logl((long double)invc);
+            const double d = (double)l, miss = (double)fabsl(l - d);
+            if (miss < best) {
+                best = miss;
+                t[2 * i] = invc;
+                t[2 * i + 1] = d;
+            }
+        }
     }
 }
 
