@@ -99,6 +99,12 @@ hipError_t launch_ln_rate_exact(int64_t n, const double* kT, const double* ne, c
 hipError_t launch_draw_append(const GridView& g, const SpeciesView& ion, const SpeciesView& el, const IonTables& tab,
                               const DrawArgs& a, const PairBuffers& pb, const DrawBuffers& b,
                               unsigned long long* counters, hipStream_t st);
+// The step's counts for the host: stats = {active ions, events, fallback ions,
+// electrons held} written to pinned host memory, and the counters cleared for
+// the next step.
+constexpr int ION_STATS = 4;
+hipError_t launch_ion_stats(const int32_t* el_count, int nsc, unsigned long long* counters, long long* stats,
+                            hipStream_t st);
 hipError_t launch_energy_loss(const GridView& g, const SpeciesView& el, const DrawBuffers& b, hipStream_t st);
 // The step with the exact rate fused (moments, rate, draw and append per
 // supercell in one kernel); ne, kT (and mom4) receive the cell moments as

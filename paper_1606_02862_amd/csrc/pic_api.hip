@@ -17,6 +17,13 @@
 
 using namespace pic;
 
+// What kernels report to the host: pinned and coherent, read after a stream
+// synchronisation, so that no copy follows the kernels of a call.
+struct HostPage {
+    int32_t flags[NFLAGS];
+    long long ion[ION_STATS];
+};
+
 struct pic_ctx {
     pic_grid_t grid{};
     int order = 1;
@@ -30,7 +37,8 @@ struct pic_ctx {
     pic_alloc_t alloc{};
     bool use_cb = false;
     std::vector<void*> owned;
-    int32_t* flags_host = nullptr;  // pinned
+    HostPage* page = nullptr;       // pinned; page_dev is its address on the device
+    HostPage* page_dev = nullptr;
     int device = 0;                 // current device at pic_init
     int64_t step = 0;
     bool rho_prev_valid = false;    // diag.rho_prev holds rho before the last cycle (PIC_OPT_CONTINUITY)
@@ -53,6 +61,7 @@ struct pic_ctx {
     double* rtab[PIC_MAX_SPECIES] = {};      // tabulated subshell sums (PIC_RATE_TABLE), built at first use
     bool rtab_ready[PIC_MAX_SPECIES] = {};
     unsigned long long* fbl[PIC_MAX_SPECIES] = {};  // per pair: rate fallback list
+    bool counters_clear = false;             // counters are all zero between ionisation steps
     unsigned long long* counters = nullptr;  // CNT_WORDS ionisation counters (fallback list, striped active / ionised)
     hipEvent_t iev[4] = {};
     // surrogate per ion species
@@ -135,8 +144,8 @@ void release_all(pic_ctx* c)
     c->ev.clear();
     for (hipEvent_t& e : c->iev)
         if (e) { (void)hipEventDestroy(e); e = nullptr; }
-    if (c->flags_host) (void)hipHostFree(c->flags_host);
-    c->flags_host = nullptr;
+    if (c->page) (void)hipHostFree(c->page);
+    c->page = nullptr;
 }
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
@@ -335,7 +344,12 @@ int alloc_ionisation(pic_ctx* c)
     const double* x = gauss_laguerre_nodes(&w);
     double rule[GL_WORDS];
     for (int k = 0; k < GL_NODES; ++k) { rule[k] = x[k]; rule[GL_NODES + k] = w[k]; }
-    log_table(rule + 2 * GL_NODES);
+    struct LogTable {
+        double t[2 * LOG_N];
+        LogTable() { log_table(t); }
+    };
+    static const LogTable lt;  // a process constant: 0.3 ms once
+    std::memcpy(rule + 2 * GL_NODES, lt.t, sizeof lt.t);
     HIPCHK(c, hipMemcpyAsync(c->gl, rule, sizeof rule, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     for (hipEvent_t& e : c->iev) HIPCHK(c, hipEventCreate(&e));
@@ -386,13 +400,11 @@ double omega_p(double n_ref_cm3)
 
 int read_flags(pic_ctx* c)
 {
-    HIPCHK(c, hipMemcpyAsync(c->flags_host, c->g.flags, NFLAGS * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     int32_t f[NFLAGS];
-    std::memcpy(f, c->flags_host, sizeof f);
+    std::memcpy(f, c->page->flags, sizeof f);
     if (f[FLAG_CAPACITY] || f[FLAG_MIGRATE] || f[FLAG_CFL] || f[FLAG_NONFINITE]) {
-        HIPCHK(c, launch_zero_i32(c->g.flags, NFLAGS, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
+        std::memset(c->page->flags, 0, sizeof f);
         if (f[FLAG_CAPACITY]) return fail(c, PIC_ERR_CAPACITY, "a supercell's frames overflowed");
         if (f[FLAG_MIGRATE]) return fail(c, PIC_ERR_CAPACITY, "a supercell's migration buffer overflowed");
         if (f[FLAG_CFL]) return fail(c, PIC_ERR_CFL, "a particle moved one cell or more in one step (or went non-finite)");
@@ -766,17 +778,25 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
         c->err = "device query or static staging buffer address failed";
         return bail(PIC_ERR_HIP);
     }
-    if (hipHostMalloc((void**)&c->flags_host, NFLAGS * sizeof(int32_t)) != hipSuccess) {
-        c->flags_host = nullptr;
+    if (hipHostMalloc((void**)&c->page, sizeof(HostPage), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        c->page = nullptr;
         c->err = "pinned host allocation failed";
         return bail(PIC_ERR_HIP);
     }
-    bool fields_ok = (g.flags = (int32_t*)dev_alloc(c, 64)) != nullptr;
+    std::memset(c->page, 0, sizeof(HostPage));
+    void* page_dev = nullptr;
+    if (hipHostGetDevicePointer(&page_dev, c->page, 0) != hipSuccess) {
+        c->err = "pinned host memory is not mapped";
+        return bail(PIC_ERR_HIP);
+    }
+    c->page_dev = (HostPage*)page_dev;
+    g.flags = c->page_dev->flags;
+    bool fields_ok;
     if (c->fp64)
-        fields_ok = fields_ok && (g64.E = (double*)dev_alloc(c, 3 * N * 8)) && (g64.B = (double*)dev_alloc(c, 3 * N * 8)) &&
+        fields_ok = (g64.E = (double*)dev_alloc(c, 3 * N * 8)) && (g64.B = (double*)dev_alloc(c, 3 * N * 8)) &&
                     (g64.J = (double*)dev_alloc(c, 3 * N * 8));
     else
-        fields_ok = fields_ok && (g.E = (float*)dev_alloc(c, 3 * N * 4)) && (g.B = (float*)dev_alloc(c, 3 * N * 4)) &&
+        fields_ok = (g.E = (float*)dev_alloc(c, 3 * N * 4)) && (g.B = (float*)dev_alloc(c, 3 * N * 4)) &&
                     (g.J = (float*)dev_alloc(c, 3 * N * 4));
     g64.flags = g.flags;
     if (!fields_ok) {
@@ -801,7 +821,7 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
                    launch_zero_f64(g64.J, 3 * N, c->stream))
                 : (launch_zero_f32(g.E, 3 * N, c->stream) || launch_zero_f32(g.B, 3 * N, c->stream) ||
                    launch_zero_f32(g.J, 3 * N, c->stream));
-    if (zero_failed || launch_zero_i32(g.flags, 16, c->stream) || launch_zero_f64(c->diag.result, D_NSLOTS, c->stream) ||
+    if (zero_failed || launch_zero_f64(c->diag.result, D_NSLOTS, c->stream) ||
         (g.J64 && launch_zero_f64(reinterpret_cast<double*>(g.J64), 3 * N, c->stream))) {
         c->err = "field initialisation launch failed";
         return bail(PIC_ERR_HIP);
@@ -1082,7 +1102,8 @@ int ionize_impl(pic_ctx* c, pic_rate_mode_t mode, bool staged, pic_ionize_stats_
         if (!ionising(c, s)) continue;
         const int e = c->sp[s].desc.ionize_into;
         const IonTables tab = ion_tables(c, s);
-        HIPCHK(c, launch_zero_i32((int32_t*)c->counters, 2 * CNT_WORDS, c->stream));
+        if (!c->counters_clear) HIPCHK(c, launch_zero_i32((int32_t*)c->counters, 2 * CNT_WORDS, c->stream));
+        c->counters_clear = false;
         HIPCHK(c, hipEventRecord(c->iev[0], c->stream));
         const pic_species_t& d = c->sp[s].desc;
         const bool eloss = d.energy_loss != 0;
@@ -1121,21 +1142,18 @@ int ionize_impl(pic_ctx* c, pic_rate_mode_t mode, bool staged, pic_ionize_stats_
         }
         if (eloss) HIPCHK(c, launch_energy_loss(c->g, c->sp[e].v, db, c->stream));
         HIPCHK(c, hipEventRecord(c->iev[3], c->stream));
-        unsigned long long cnt[CNT_WORDS];
-        HIPCHK(c, hipMemcpyAsync(cnt, c->counters, sizeof cnt, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, launch_ion_stats(c->sp[e].v.count, c->g.nsc, c->counters, c->page_dev->ion, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        c->counters_clear = true;
         float r = -1.f, t = 0.f;
         if (!fused) HIPCHK(c, hipEventElapsedTime(&r, c->iev[1], c->iev[2]));
         HIPCHK(c, hipEventElapsedTime(&t, c->iev[0], c->iev[3]));
         rate_ms += r;
         total_ms += t;
-        for (int k = 0; k < CNT_STRIPES; ++k) {
-            st.ions_active += (int64_t)cnt[CNT_ACTIVE + k];
-            st.ionized += (int64_t)cnt[CNT_FIRED + k];
-            st.fallback += (int64_t)cnt[CNT_FBIONS + k];
-        }
-        std::vector<int32_t> cc;
-        st.electrons = host_count(c, e, cc);
+        st.ions_active += c->page->ion[0];
+        st.ionized += c->page->ion[1];
+        st.fallback += c->page->ion[2];
+        st.electrons = c->page->ion[3];
         c->sp[e].wmax = std::max(c->sp[e].wmax, c->sp[s].wmax);  // born electrons carry ion weights
         c->sp[e].wheld = std::max(c->sp[e].wheld, c->sp[s].wheld);
     }

@@ -40,7 +40,7 @@ struct GridViewT {
     R* E;                  // 3 * N, component-major, x fastest
     R* B;
     R* J;
-    int32_t* flags;
+    int32_t* flags;        // NFLAGS, in pinned host memory (kernels store to it on an error only)
     typename Vec4<R>::type* qbuf;  // deposit queue: nsc * qcap records of 2 (x0,y0,z0,qw | x1,y1,z1,-)
     int qcap;              // queue slots per supercell (>= every species' frame capacity; a multiple of 512)
     // PIC_OPT_DETERMINISTIC_J (FP32): 3 * N int64 fixed-point current at the
