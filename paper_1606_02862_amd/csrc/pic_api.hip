@@ -32,6 +32,10 @@ struct pic_ctx {
     GridView g{};          // geometry always; FP32 field pointers in FP32 mode
     GridView64 g64{};      // FP64 mode: geometry and field pointers
     bool fp64 = false;
+    FieldScratchT<float> fs{};
+    FieldScratchT<double> fs64{};
+    bool fused = false;             // the fused field update (its scratch is held)
+    bool jacc_clear = false;        // fused: the current accumulators (or J64) are all zero
     DiagBuffers diag{};
     hipStream_t stream = nullptr;
     pic_alloc_t alloc{};
@@ -253,6 +257,9 @@ int alloc_real_arrays(pic_ctx* c, int s, SpeciesViewT<R>& v, size_t n, size_t ni
 template <class R> GridViewT<R>& gview(pic_ctx* c);
 template <> GridView& gview<float>(pic_ctx* c) { return c->g; }
 template <> GridView64& gview<double>(pic_ctx* c) { return c->g64; }
+template <class R> FieldScratchT<R>& fscratch(pic_ctx* c);
+template <> FieldScratchT<float>& fscratch<float>(pic_ctx* c) { return c->fs; }
+template <> FieldScratchT<double>& fscratch<double>(pic_ctx* c) { return c->fs64; }
 template <class R> SpeciesViewT<R>& sview(pic_ctx* c, int s);
 template <> SpeciesView& sview<float>(pic_ctx* c, int s) { return c->sp[s].v; }
 template <> SpeciesView64& sview<double>(pic_ctx* c, int s) { return c->sp[s].v64; }
@@ -649,6 +656,7 @@ template <class R>
 int step_t(pic_ctx* c, int n)
 {
     GridViewT<R>& g = gview<R>(c);
+    const FieldScratchT<R>& fs = fscratch<R>(c);
     const int64_t N = (int64_t)c->grid.nx * c->grid.ny * c->grid.nz;
     const double dt = c->grid.dt;
     for (int it = 0; it < n; ++it) {
@@ -666,28 +674,43 @@ int step_t(pic_ctx* c, int n)
                 if (c->sp[s].desc.mobile) vg = std::max(vg, push_vmax(c, s));
             jscale_g = fixed_scale(vg);
             g.jinv64 = 1.0 / (double)jscale_g;
-            HIPCHK(c, launch_zero_f64(reinterpret_cast<double*>(g.J64), 3 * N, c->stream));  // all-zero bits
-        } else {
-            HIPCHK(c, launch_zero_r(g.J, 3 * N, c->stream));
         }
+        // the deposit's accumulators; fused: cleared by the previous cycle's field update
+        // (not before the first cycle or after a failed launch)
+        GridViewT<R> gp = g;
+        if (c->fused) gp.J = fs.Jacc;
+        if (!c->jacc_clear) {
+            if (g.J64) HIPCHK(c, launch_zero_f64(reinterpret_cast<double*>(g.J64), 3 * N, c->stream));  // all-zero bits
+            else HIPCHK(c, launch_zero_r(gp.J, 3 * N, c->stream));
+        }
+        c->jacc_clear = false;
         // step `it` writes its leavers to parity it & 1 and absorbs the previous step's
         const int wpar = it & 1, apar = it > 0 ? ((it - 1) & 1) : -1;
         for (int s = 0; s < c->nsp; ++s) {
             if (!c->sp[s].desc.mobile) continue;
-            HIPCHK(c, launch_push<R>(g, sview<R>(c, s), c->order, c->grid.gather == PIC_GATHER_GALERKIN,
+            HIPCHK(c, launch_push<R>(gp, sview<R>(c, s), c->order, c->grid.gather == PIC_GATHER_GALERKIN,
                                      push_vmax(c, s), jscale_g, apar, wpar, c->stream));
             c->pending_launches += c->timing ? 1 : 0;
         }
         if (c->timing) HIPCHK(c, hipEventRecord(e1, c->stream));
-        if (it == n - 1)  // last step of the call: leave the frames dense
-            for (int s = 0; s < c->nsp; ++s) {
-                if (!c->sp[s].desc.mobile) continue;
-                HIPCHK(c, launch_migrate<R>(g, sview<R>(c, s), wpar, c->stream));
-            }
+        const bool last = it == n - 1;  // of the call: leave the frames dense, keep J
+        MigrateArgsT<R> mig{};
+        mig.par = wpar;
+        for (int s = 0; last && s < c->nsp; ++s) {
+            if (!c->sp[s].desc.mobile) continue;
+            if (c->fused && !c->timing) mig.s[mig.n++] = sview<R>(c, s);
+            else HIPCHK(c, launch_migrate<R>(g, sview<R>(c, s), wpar, c->stream));
+        }
         if (c->timing) HIPCHK(c, hipEventRecord(e2, c->stream));
-        HIPCHK(c, launch_yee_b<R>(g, 0.5 * dt, c->stream));
-        HIPCHK(c, launch_yee_e<R>(g, dt, c->stream));
-        HIPCHK(c, launch_yee_b<R>(g, 0.5 * dt, c->stream));
+        if (c->fused) {
+            HIPCHK(c, launch_yee_head<R>(g, fs, dt, last, c->stream));
+            HIPCHK(c, launch_yee_tail<R>(g, fs, mig, dt, c->stream));
+            c->jacc_clear = true;
+        } else {
+            HIPCHK(c, launch_yee_b<R>(g, 0.5 * dt, c->stream));
+            HIPCHK(c, launch_yee_e<R>(g, dt, c->stream));
+            HIPCHK(c, launch_yee_b<R>(g, 0.5 * dt, c->stream));
+        }
         if (c->timing) HIPCHK(c, hipEventRecord(e3, c->stream));
         ++c->step;
     }
@@ -799,6 +822,13 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
         fields_ok = (g.E = (float*)dev_alloc(c, 3 * N * 4)) && (g.B = (float*)dev_alloc(c, 3 * N * 4)) &&
                     (g.J = (float*)dev_alloc(c, 3 * N * 4));
     g64.flags = g.flags;
+    const size_t fbytes = (size_t)3 * N * (c->fp64 ? 8 : 4);
+    void* fsp[3] = {};
+    c->fused = N <= FUSE_CELLS;
+    for (void*& p : fsp)
+        if (c->fused) fields_ok = fields_ok && (p = dev_alloc(c, fbytes));
+    c->fs = FieldScratchT<float>{(float*)fsp[0], (float*)fsp[1], (float*)fsp[2]};
+    c->fs64 = FieldScratchT<double>{(double*)fsp[0], (double*)fsp[1], (double*)fsp[2]};
     if (!fields_ok) {
         c->err = "device allocation of fields failed";
         return bail(PIC_ERR_OOM);

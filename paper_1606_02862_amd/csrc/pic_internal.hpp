@@ -44,8 +44,8 @@ struct GridViewT {
     typename Vec4<R>::type* qbuf;  // deposit queue: nsc * qcap records of 2 (x0,y0,z0,qw | x1,y1,z1,-)
     int qcap;              // queue slots per supercell (>= every species' frame capacity; a multiple of 512)
     // PIC_OPT_DETERMINISTIC_J (FP32): 3 * N int64 fixed-point current at the
-    // cycle's common scale, which the E update converts (times jinv64) into J;
-    // nullptr otherwise
+    // cycle's common scale, which the field update converts (times jinv64) into
+    // J and clears; nullptr otherwise
     unsigned long long* J64;
     double jinv64;
 };
@@ -139,6 +139,27 @@ template <class R>
 hipError_t launch_yee_b(const GridViewT<R>& g, double coef, hipStream_t st);
 template <class R>
 hipError_t launch_yee_e(const GridViewT<R>& g, double coef, hipStream_t st);
+// The fused field update (k_fields.hip), for grids of up to FUSE_CELLS cells.
+// Scratch of 3 * N values each: the fields between its two kernels, and the
+// current accumulators the deposit adds to, zero between cycles (unused with
+// g.J64, whose sums are cleared the same way).
+constexpr int64_t FUSE_CELLS = 1 << 20;
+template <class R>
+struct FieldScratchT {
+    R *E, *B, *Jacc;
+};
+// Species whose arrivals of parity par the tail's first workgroups absorb.
+template <class R>
+struct MigrateArgsT {
+    SpeciesViewT<R> s[PIC_MAX_SPECIES];
+    int n, par;
+};
+// keep_j: write J as well as use it
+template <class R>
+hipError_t launch_yee_head(const GridViewT<R>& g, const FieldScratchT<R>& f, double dt, bool keep_j, hipStream_t st);
+template <class R>
+hipError_t launch_yee_tail(const GridViewT<R>& g, const FieldScratchT<R>& f, const MigrateArgsT<R>& mig,
+                           double dt, hipStream_t st);
 
 // FP64 diagnostics.  partial buffers hold one entry per workgroup.
 struct DiagBuffers {
