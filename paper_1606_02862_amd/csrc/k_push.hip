@@ -178,12 +178,22 @@ __device__ inline void flush_node(const GridView& g, int i, long long iv, float 
     }
 }
 
+// Two variants.  The default: one workgroup per supercell, arrivals of the
+// previous step absorbed first.  SPLIT, for grids of few supercells, which
+// leave most of the chip idle: `parts` workgroups of SPLIT_NT lanes per
+// supercell, part p taking every parts-th frame from frame p.  Each stages the
+// fields and flushes a current tile of its own (the flush adds atomically
+// already); the supercell's hole list is shared, each part reserving its
+// range after its frame loop from a list of its own in LDS; the frames are
+// dense when the kernel starts, since the field update's last kernel absorbs
+// the arrivals of every cycle.
+//
 // Waves per SIMD the register budget is fitted to: 4 in FP32, 2 in FP64.
 template <class R> constexpr int push_waves() { return std::is_same<R, float>::value ? 4 : 2; }
 
-template <int ORDER, bool HAS_Z, bool GAL, int NT, class R>
+template <int ORDER, bool HAS_Z, bool GAL, int NT, class R, bool SPLIT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(push_waves<R>())))
-void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, int apar, int wpar)
+void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, int apar, int wpar, int parts)
 {
     using T = Tile<ORDER, R>;
     using A = JAcc<R>;
@@ -208,9 +218,14 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     constexpr int NW = NT / 64;
     __shared__ int s_qn[NW], s_qo[NW];
 
-    const int sc = sc_of_block(blockIdx.x, g.nsc, g.ncx * g.ncy, g.xcd_remap);
+    // SPLIT: this part's frames begin at f0 and advance by fstep
+    const int part = SPLIT ? (int)blockIdx.x / g.nsc : 0;
+    const int f0 = part * NT, fstep = SPLIT ? parts * NT : NT;
+    const int sc = sc_of_block((int)blockIdx.x - part * g.nsc, g.nsc, g.ncx * g.ncy, g.xcd_remap);
+    __shared__ int s_left[SPLIT ? max_cap_in(ORDER) : 1];  // SPLIT: slots of this part's leavers
+    __shared__ int s_hbase;                                // and its range of the hole list
     // arrivals of the previous step first (frames dense again before pushing)
-    if (apar >= 0) fill_supercell<NT>(g, s, sc, apar, reinterpret_cast<int*>(smem), s_cnt);
+    if (!SPLIT && apar >= 0) fill_supercell<NT>(g, s, sc, apar, reinterpret_cast<int*>(smem), s_cnt);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
@@ -243,13 +258,14 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     if (tid == 0) { s_holes = 0; s_queue = 0; s_queue_m = 0; }
     __syncthreads();
     const int wave = tid >> 6;
-    const int rw = g.qcap / NW;  // queue region of one wave: >= its slots of every frame
+    const int qreg = SPLIT ? g.qcap / parts : g.qcap;  // the workgroup's region of the queue: >= its slots
+    const int rw = qreg / NW;    // queue region of one wave: >= its slots of every frame
     int qn = 0;                  // records this wave has queued (the same in all its active lanes):
     int qo = 0;                  // qn single-axis crossers from the front of its region, qo others from the back
 
     const int n = s.count[sc];
     const int64_t base = (int64_t)sc * s.cap;
-    const int64_t qbase = (int64_t)sc * g.qcap;
+    const int64_t qbase = (int64_t)sc * g.qcap + part * qreg;
     const R dt = g.dt;
     const R cdx = dt / g.dx, cdy = dt / g.dy, cdz = dt / g.dz;
     const R inv_dvdt = R(1) / (g.dx * g.dy * g.dz * dt);
@@ -275,7 +291,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     // two register sets alternate and the loop is unrolled by two, so the loads of
     // frame f + 2 are in flight during frame f and no register is copied
     // before its load has returned; otherwise one set holds frame f + 1.
-    constexpr bool DEPTH2 = std::is_same<R, float>::value && ORDER <= 2;
+    constexpr bool DEPTH2 = std::is_same<R, float>::value && ORDER <= 2 && !SPLIT;
     struct Part {
         R x, y, z, ux, uy, uz, w;
         int zs;
@@ -438,7 +454,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
                 mb = __shfl(mb, leader, 64);
                 if (!same && valid) {
                     const bool one = nax == 1;
-                    const int slot = one ? sb + __popcll(smask & below) : g.qcap - 1 - (mb + __popcll(mmask & below));
+                    const int slot = one ? sb + __popcll(smask & below) : qreg - 1 - (mb + __popcll(mmask & below));
                     const R ax = one ? R(fx1 != inx ? 0 : fy1 != iny ? 1 : 2) : R(-1);
                     R4* e = g.qbuf + 2 * (qbase + slot);
                     e[0] = make4(x0, y0, z0, qw);
@@ -474,7 +490,8 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
             const int hidx = hb + __popcll(lmask & ((1ull << lane) - 1ull));
             if (left) {
                 if (hidx < s.cap_in) {
-                    s.holes[(int64_t)sc * s.cap_in + hidx] = slot;
+                    if constexpr (SPLIT) s_left[hidx] = slot;
+                    else s.holes[(int64_t)sc * s.cap_in + hidx] = slot;
                 } else {
                     // hole list full (reported through FLAG_MIGRATE below): keep the
                     // particle inside its supercell so every later access stays in bounds
@@ -487,7 +504,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     };
     Part pa{}, pb{};
     if (n > 0) {  // block-uniform; lanes past the end load the last particle again
-        pa = load_part(tid < n ? tid : n - 1);
+        pa = load_part(f0 + tid < n ? f0 + tid : n - 1);
         if constexpr (DEPTH2) {
             pb = load_part(NT + tid < n ? NT + tid : n - 1);
             // set A has arrived, set B stays in flight: the loop's waits then
@@ -524,11 +541,11 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
         }
     } else {
         (void)pb;
-        for (int f = 0; f < n; f += NT) {
+        for (int f = f0; f < n; f += fstep) {
             const int slot = f + tid;
             if (slot >= n) break;
             const Part cur = pa;
-            pa = load_part(slot + NT < n ? slot + NT : n - 1);
+            pa = load_part(slot + fstep < n ? slot + fstep : n - 1);
             push_one(slot, cur, true);
         }
     }
@@ -579,7 +596,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     } else if constexpr (QCLASS) {  // single-axis crossers (front), then the others (back)
         const int n1 = s_queue, nm = s_queue_m;
         for (int t = tid; t < n1; t += NT) queued(t, true);
-        for (int t = tid; t < nm; t += NT) queued(g.qcap - 1 - t, false);
+        for (int t = tid; t < nm; t += NT) queued(qreg - 1 - t, false);
     } else {
         const int nq = s_queue;
         for (int t = tid; t < nq; t += NT) queued(t, false);
@@ -587,9 +604,25 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
 
     // ---- hand the leavers to their destination supercells' arrival lists
     const int nh = min(s_holes, s.cap_in);
+    if constexpr (SPLIT) {  // this part's range of the supercell's hole list
+        if (tid == 0) s_hbase = nh ? atomicAdd(&s.hole_count[sc], nh) : 0;
+        __syncthreads();
+    }
     for (int t = tid; t < nh; t += NT) {
-        const int slot = s.holes[(int64_t)sc * s.cap_in + t];
+        const int slot = SPLIT ? s_left[t] : s.holes[(int64_t)sc * s.cap_in + t];
         const int64_t p = base + slot;
+        if constexpr (SPLIT) {
+            const int hidx = s_hbase + t;
+            if (hidx < s.cap_in) {
+                s.holes[(int64_t)sc * s.cap_in + hidx] = slot;
+            } else {  // the parts together overflow the list: as for one part above
+                s.x[p] = rmin(rmax(s.x[p], R(0)), xm);
+                s.y[p] = rmin(rmax(s.y[p], R(0)), ym);
+                s.z[p] = rmin(rmax(s.z[p], R(0)), zm);
+                g.flags[FLAG_MIGRATE] = 1;
+                continue;
+            }
+        }
         const R x1 = s.x[p], y1 = s.y[p], z1 = s.z[p];
         const R lux = s.ux[p], luy = s.uy[p], luz = s.uz[p], lw = s.w[p];
         const uint32_t lid = s.id[p];
@@ -683,35 +716,40 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     }
     if (tid == 0) {
         const int h = s_holes;
-        s.hole_count[sc] = h < s.cap_in ? h : s.cap_in;
+        if (!SPLIT) s.hole_count[sc] = h < s.cap_in ? h : s.cap_in;
         if (h > s.cap_in) g.flags[FLAG_MIGRATE] = 1;
     }
 }
 
-template <int ORDER, int NT, class R>
+template <int ORDER, int NT, class R, bool SPLIT>
 static void launch_push_order(const GridViewT<R>& g, const SpeciesViewT<R>& s, bool gal, R jscale, R jinv,
-                              double jratio, int apar, int wpar, hipStream_t st)
+                              double jratio, int apar, int wpar, int parts, hipStream_t st)
 {
-    const dim3 grid(g.nsc), block(NT);
+    const dim3 grid(g.nsc * (SPLIT ? parts : 1)), block(NT);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, g, s, jscale, jinv, jratio, apar, wpar, parts);
+    };
     const bool hz = s.zs != nullptr;
     if (gal) {
-        if (hz) hipLaunchKernelGGL((k_push<ORDER, true, true, NT, R>), grid, block, 0, st, g, s, jscale, jinv, jratio, apar, wpar);
-        else hipLaunchKernelGGL((k_push<ORDER, false, true, NT, R>), grid, block, 0, st, g, s, jscale, jinv, jratio, apar, wpar);
+        if (hz) go(k_push<ORDER, true, true, NT, R, SPLIT>);
+        else go(k_push<ORDER, false, true, NT, R, SPLIT>);
     } else {
-        if (hz) hipLaunchKernelGGL((k_push<ORDER, true, false, NT, R>), grid, block, 0, st, g, s, jscale, jinv, jratio, apar, wpar);
-        else hipLaunchKernelGGL((k_push<ORDER, false, false, NT, R>), grid, block, 0, st, g, s, jscale, jinv, jratio, apar, wpar);
+        if (hz) go(k_push<ORDER, true, false, NT, R, SPLIT>);
+        else go(k_push<ORDER, false, false, NT, R, SPLIT>);
     }
 }
 
 template <class R>
 hipError_t launch_push(const GridViewT<R>& g, const SpeciesViewT<R>& s, int order, bool galerkin, double vmax,
-                       float jscale_g, int apar, int wpar, hipStream_t st)
+                       float jscale_g, int apar, int wpar, int parts, hipStream_t st)
 {
     // the deposit queue holds a full supercell, split evenly over the waves of a workgroup
     const int nt = order == 1 ? 256 : 512;
     // whole frames per slab: the paired frame loop runs every lane of a pair's
     // second frame, and a lane past the count stores into its own free slot
     if (s.cap % nt != 0 || s.cap > g.qcap || g.qcap % (nt / 64) != 0) return hipErrorInvalidValue;
+    // SPLIT: dense frames, and room in a part's region of the queue for its share of full frames
+    if (parts < 0 || (parts > 0 && (apar >= 0 || g.qcap / parts < split_region(s.cap, parts)))) return hipErrorInvalidValue;
     if (s.cap_in > max_cap_in(order)) return hipErrorInvalidValue;
     R jscale = R(1), jinv = R(1);
     double jratio = 1.0;
@@ -725,15 +763,23 @@ hipError_t launch_push(const GridViewT<R>& g, const SpeciesViewT<R>& s, int orde
             jratio = (double)jscale_g / (double)jscale;
         }
     }
-    if (order == 1) launch_push_order<1, 256>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, st);
-    else if (order == 2) launch_push_order<2, 512>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, st);
-    else launch_push_order<3, 512>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, st);
+    // a tile rescaled to the common scale is rounded once per node: order-independent only as one tile per supercell
+    if (parts > 1 && jratio != 1.0) parts = 1;
+    if (parts > 0) {
+        if (order == 1) launch_push_order<1, SPLIT_NT, R, true>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, parts, st);
+        else if (order == 2) launch_push_order<2, SPLIT_NT, R, true>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, parts, st);
+        else launch_push_order<3, SPLIT_NT, R, true>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, parts, st);
+    } else {
+        if (order == 1) launch_push_order<1, 256, R, false>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, 1, st);
+        else if (order == 2) launch_push_order<2, 512, R, false>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, 1, st);
+        else launch_push_order<3, 512, R, false>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, 1, st);
+    }
     return hipGetLastError();
 }
 
 template hipError_t launch_push<float>(const GridView&, const SpeciesView&, int, bool, double, float, int, int,
-                                       hipStream_t);
+                                       int, hipStream_t);
 template hipError_t launch_push<double>(const GridView64&, const SpeciesView64&, int, bool, double, float, int, int,
-                                        hipStream_t);
+                                        int, hipStream_t);
 
 }  // namespace pic

@@ -34,6 +34,7 @@ struct pic_ctx {
     bool fp64 = false;
     FieldScratchT<float> fs{};
     FieldScratchT<double> fs64{};
+    bool split = false;             // the particle kernel's split variant (implies fused)
     bool fused = false;             // the fused field update (its scratch is held)
     bool jacc_clear = false;        // fused: the current accumulators (or J64) are all zero
     DiagBuffers diag{};
@@ -685,18 +686,19 @@ int step_t(pic_ctx* c, int n)
         }
         c->jacc_clear = false;
         // step `it` writes its leavers to parity it & 1 and absorbs the previous step's
-        const int wpar = it & 1, apar = it > 0 ? ((it - 1) & 1) : -1;
+        // (split: every step's arrivals are absorbed at its end instead)
+        const int wpar = it & 1, apar = it > 0 && !c->split ? ((it - 1) & 1) : -1;
         for (int s = 0; s < c->nsp; ++s) {
             if (!c->sp[s].desc.mobile) continue;
             HIPCHK(c, launch_push<R>(gp, sview<R>(c, s), c->order, c->grid.gather == PIC_GATHER_GALERKIN,
-                                     push_vmax(c, s), jscale_g, apar, wpar, c->stream));
+                                     push_vmax(c, s), jscale_g, apar, wpar, c->sp[s].parts, c->stream));
             c->pending_launches += c->timing ? 1 : 0;
         }
         if (c->timing) HIPCHK(c, hipEventRecord(e1, c->stream));
         const bool last = it == n - 1;  // of the call: leave the frames dense, keep J
         MigrateArgsT<R> mig{};
         mig.par = wpar;
-        for (int s = 0; last && s < c->nsp; ++s) {
+        for (int s = 0; (last || c->split) && s < c->nsp; ++s) {
             if (!c->sp[s].desc.mobile) continue;
             if (c->fused && !c->timing) mig.s[mig.n++] = sview<R>(c, s);
             else HIPCHK(c, launch_migrate<R>(g, sview<R>(c, s), wpar, c->stream));
@@ -874,7 +876,12 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
     }
     // one deposit queue shared by the species (their particle kernels run one after another)
     g.qcap = 0;
-    for (int s = 0; s < n_species; ++s) g.qcap = std::max(g.qcap, c->sp[s].v.cap);
+    c->split = c->fused && split_parts(g.nsc, 1) > 0;
+    for (int s = 0; s < n_species; ++s) {
+        Species& S = c->sp[s];
+        S.parts = c->split ? split_parts(g.nsc, S.desc.ppc > 0 ? S.desc.ppc * SC_CELLS : S.v.cap) : 0;
+        g.qcap = std::max(g.qcap, S.parts ? S.parts * split_region(S.v.cap, S.parts) : S.v.cap);
+    }
     g.qcap = (g.qcap + 511) / 512 * 512;  // whole 512-lane workgroups' worth of slots
     g64.qcap = g.qcap;
     const bool q_ok = c->fp64 ? (g64.qbuf = (double4*)dev_alloc(c, (size_t)2 * g.nsc * g.qcap * sizeof(double4))) != nullptr

@@ -42,7 +42,7 @@ struct GridViewT {
     R* J;
     int32_t* flags;        // NFLAGS, in pinned host memory (kernels store to it on an error only)
     typename Vec4<R>::type* qbuf;  // deposit queue: nsc * qcap records of 2 (x0,y0,z0,qw | x1,y1,z1,-)
-    int qcap;              // queue slots per supercell (>= every species' frame capacity; a multiple of 512)
+    int qcap;              // queue slots per supercell (>= every species' frame capacity, in whole frames of a part)
     // PIC_OPT_DETERMINISTIC_J (FP32): 3 * N int64 fixed-point current at the
     // cycle's common scale, which the field update converts (times jinv64) into
     // J and clears; nullptr otherwise
@@ -87,6 +87,7 @@ struct Species {
     pic_species_t desc;
     int64_t n_init;        // particles at t = 0
     int64_t id_offset;     // first id at t = 0
+    int parts;             // workgroups per supercell in the particle kernel (split_parts)
     double weight;
     double wmax;           // bound of |w| that sets the fixed-point current scale (>= wheld)
     double wheld;          // largest |w| known to be held (init, set, ionisation electrons)
@@ -124,9 +125,27 @@ inline hipError_t launch_zero_r(double* p, int64_t n, hipStream_t st) { return l
 // galerkin: the reduced-order gather along staggered axes (PIC_GATHER_GALERKIN)
 // jscale_g: with g.J64, the cycle's common fixed-point scale (2^30 over the
 // largest vmax of the cycle's species); each tile is rescaled to it at the flush
+// parts: 0 for one workgroup per supercell; else the workgroups of SPLIT_NT
+// lanes that share one (the arrivals then absorbed before the launch, apar = -1)
 template <class R>
 hipError_t launch_push(const GridViewT<R>& g, const SpeciesViewT<R>& s, int order, bool galerkin, double vmax,
-                       float jscale_g, int apar, int wpar, hipStream_t st);
+                       float jscale_g, int apar, int wpar, int parts, hipStream_t st);
+constexpr int SPLIT_NT = 512;
+// Queue slots a part needs: its share of a full slab, in whole frames.
+inline int split_region(int cap, int parts)
+{
+    const int per = SPLIT_NT * parts;
+    return (cap + per - 1) / per * SPLIT_NT;
+}
+// The parts of a supercell of a species with about n particles per supercell,
+// 0 where the default variant is the better one.
+inline int split_parts(int nsc, int n)
+{
+    constexpr int WGS = 512;  // two workgroups of SPLIT_NT lanes per CU
+    if (nsc > WGS) return 0;
+    const int frames = (n + SPLIT_NT - 1) / SPLIT_NT, most = WGS / nsc;
+    return frames < 1 ? 1 : frames < most ? frames : most;
+}
 // Fixed-point scale of a current tile: 2^30 over the bound vmax of one contribution.
 inline float fixed_scale(double vmax)
 {

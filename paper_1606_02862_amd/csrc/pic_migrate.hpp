@@ -38,7 +38,8 @@ __device__ inline int fill_supercell(const GridViewT<R>& g, const SpeciesViewT<R
     unsigned* s_mark = (unsigned*)(s_src + s.cap_in);
     const int tid = threadIdx.x;
     const int n = s.count[sc];
-    const int h = s.hole_count[sc];
+    int h = s.hole_count[sc];
+    if (h > s.cap_in) h = s.cap_in;  // overflow already flagged by the particle kernel
     int m = s.in_count[par * g.nsc + sc];
     if (m > s.cap_in) m = s.cap_in;  // overflow already flagged by the particle kernel
     int np = n - h + m;
