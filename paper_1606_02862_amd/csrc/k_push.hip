@@ -180,7 +180,7 @@ __device__ inline void flush_node(const GridView& g, int i, long long iv, float 
 
 // Two variants.  The default: one workgroup per supercell, arrivals of the
 // previous step absorbed first.  SPLIT, for grids of few supercells, which
-// leave most of the chip idle: `parts` workgroups of SPLIT_NT lanes per
+// leave most of the chip idle (split_parts): `parts` workgroups of SPLIT_NT lanes per
 // supercell, part p taking every parts-th frame from frame p.  Each stages the
 // fields and flushes a current tile of its own (the flush adds atomically
 // already); the supercell's hole list is shared, each part reserving its

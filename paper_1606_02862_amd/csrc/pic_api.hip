@@ -876,10 +876,10 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
     }
     // one deposit queue shared by the species (their particle kernels run one after another)
     g.qcap = 0;
-    c->split = c->fused && split_parts(g.nsc, 1) > 0;
     for (int s = 0; s < n_species; ++s) {
         Species& S = c->sp[s];
-        S.parts = c->split ? split_parts(g.nsc, S.desc.ppc > 0 ? S.desc.ppc * SC_CELLS : S.v.cap) : 0;
+        S.parts = c->fused ? split_parts(g.nsc, S.desc.ppc > 0 ? S.desc.ppc * SC_CELLS : S.v.cap, c->order) : 0;
+        c->split = c->split || S.parts > 0;
         g.qcap = std::max(g.qcap, S.parts ? S.parts * split_region(S.v.cap, S.parts) : S.v.cap);
     }
     g.qcap = (g.qcap + 511) / 512 * 512;  // whole 512-lane workgroups' worth of slots

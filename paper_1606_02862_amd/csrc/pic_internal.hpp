@@ -138,13 +138,28 @@ inline int split_region(int cap, int parts)
     return (cap + per - 1) / per * SPLIT_NT;
 }
 // The parts of a supercell of a species with about n particles per supercell,
-// 0 where the default variant is the better one.
-inline int split_parts(int nsc, int n)
+// 0 for the default variant.  Up to 512 supercells: the number that makes the
+// fullest CU's work least, its workgroups (of 256 CUs) times the frames of
+// each plus 3 for the staging, clearing and flush of a tile (fitted to the
+// figures below).  One part is the default's work on 512 lanes, better than its
+// 256 for CIC only.  Measured, two cycles with 16 particles per cell (default
+// against 1, 2, 4, 8 parts; us):
+//   TSC  16 supercells 155 / 74 (8), 125: 164 / 126 (2), 130 (4), 152 (8),
+//        256: 176 / 178 (1), 203 (4), 384: 275 / 279 (1), 240 (2), 640: 374 / 384 (1);
+//   CIC  64 supercells 97 / 64 (4), 70 (8), 256: 107 / 96 (1), 640: 165 / 176 (1);
+// with 4 per cell TSC 384: 118 / 118 (1), 136 (2).
+inline int split_parts(int nsc, int n, int order)
 {
-    constexpr int WGS = 512;  // two workgroups of SPLIT_NT lanes per CU
-    if (nsc > WGS) return 0;
-    const int frames = (n + SPLIT_NT - 1) / SPLIT_NT, most = WGS / nsc;
-    return frames < 1 ? 1 : frames < most ? frames : most;
+    constexpr int CUS = 256, TILE = 3;
+    if (nsc > 2 * CUS) return 0;
+    const int frames = n > SPLIT_NT ? (n + SPLIT_NT - 1) / SPLIT_NT : 1;
+    int best = 1;
+    int64_t least = INT64_MAX;
+    for (int p = 1; p <= frames && (int64_t)nsc * p <= 4 * CUS; ++p) {
+        const int64_t cost = ((int64_t)nsc * p + CUS - 1) / CUS * (TILE + (frames + p - 1) / p);
+        if (cost < least) { least = cost; best = p; }
+    }
+    return best == 1 && order > 1 ? 0 : best;
 }
 // Fixed-point scale of a current tile: 2^30 over the bound vmax of one contribution.
 inline float fixed_scale(double vmax)
