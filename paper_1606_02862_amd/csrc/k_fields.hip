@@ -9,7 +9,7 @@
 // scalars from the neighbouring groups (wrapped).
 //
 // Two forms.  Large grids: three passes in place (k_yee_b, k_yee_e, k_yee_b),
-// bound by HBM.  Grids of up to FUSE_CELLS cells, bound by launches (5 us each,
+// bound by HBM.  Components of up to FUSE_BYTES, bound by launches (5 us each,
 // whatever they do): two kernels,
 //   head: B1 = B - curl E dt/2 at the group's cells and, computed again, at the
 //         neighbours that curl B1 needs; E1 = E + dt (curl B1 - J); B1 and E1 go
@@ -20,10 +20,10 @@
 //         migration (pic_migrate.hpp), in workgroups of its own, first in the
 //         grid so that the field groups run beside them.
 // A cycle with its migration is then 3 launches instead of 6 (one species).
-// Measured, one cycle on 16^3: 50.9 -> 43 us; four cycles of two species on
-// 56x40x28: 248 -> 231 us; two cycles on 64^3 in FP64 -1.3 %; on 128^3 the two
-// forms are equal (57 against 59 us of field work per cycle) and on
-// 256x256x128 the fused one, which moves J once more, is 2 % of a cycle slower.
+// Measured, passes in place against fused, one cycle (us): FP32 16^3 50.9 / 43,
+// 64^3 with 7 particles per cell 81 / 73, 96x64x64 107 / 99, 128x96x64
+// 169 / 165, 128^3 with 16 equal, 256x256x128 1 % slower (the fused form moves J
+// once more); FP64 64^3 118 / 110, 96x64x64 145 / 144, 128x64x64 199 / 205.
 #include "pic_migrate.hpp"
 
 namespace pic {

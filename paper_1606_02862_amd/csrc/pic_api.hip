@@ -487,6 +487,72 @@ int64_t host_count(pic_ctx* c, int s, std::vector<int32_t>& counts)
     return t;
 }
 
+// The species' particles in id order by way of k_export.hip.  Returns false,
+// with rc untouched, where the host has to sort (duplicate or very sparse ids,
+// no device memory for the scratch); else true with rc the result.
+template <class R, class V>
+bool export_particles(pic_ctx* c, int s, V* v, int& rc)
+{
+    using U = typename std::remove_pointer<decltype(v->ux)>::type;
+    const SpeciesViewT<R>& sv = sview<R>(c, s);
+    const int nsc = c->g.nsc;
+    if ((int64_t)nsc * sv.cap > 0xFFFFFFFFLL) return false;
+    struct Scratch {  // given back on every path
+        pic_ctx* c;
+        void* p[4] = {};
+        ~Scratch() { for (void* q : p) dev_free(c, q); }
+    } m{c};
+    auto run = [&](hipError_t e, const char* what) {
+        if (e == hipSuccess) return true;
+        rc = fail(c, PIC_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
+        return false;
+    };
+    unsigned long long st[3] = {};
+    unsigned long long* stats = (unsigned long long*)(m.p[0] = dev_alloc(c, sizeof st));
+    if (!stats) return false;
+    auto read_stats = [&] {
+        return run(hipMemcpyAsync(st, stats, sizeof st, hipMemcpyDeviceToHost, c->stream), "particle statistics") &&
+               run(hipStreamSynchronize(c->stream), "particle statistics");
+    };
+    if (!run(launch_zero_i32((int32_t*)stats, 6, c->stream), "particle statistics") ||
+        !run(launch_export_stats(sv.id, sv.count, nsc, sv.cap, stats, c->stream), "particle statistics") || !read_stats())
+        return true;
+    const int64_t total = (int64_t)st[2], words = export_words((uint32_t)st[0]);
+    if (total == 0 || words > 16 * total + (1 << 18)) return false;
+    if (v->count = total; v->capacity < total) {
+        rc = fail(c, PIC_ERR_ARG, "view capacity %lld < %lld particles", (long long)v->capacity, (long long)total);
+        return true;
+    }
+    const int64_t chunk = std::min<int64_t>(total, EXPORT_CHUNK);
+    constexpr size_t REC = 4 * 8 + 4 * sizeof(U) + 4;
+    uint32_t* bits = (uint32_t*)(m.p[1] = dev_alloc(c, (size_t)words * 4 * 2 + (size_t)(words / 1024 + 1) * 4));
+    uint32_t* perm = (uint32_t*)(m.p[2] = dev_alloc(c, (size_t)total * 4));
+    char* stage = (char*)(m.p[3] = dev_alloc(c, (size_t)chunk * REC));
+    if (!bits || !perm || !stage) return false;
+    if (!run(launch_export_rank(sv.id, sv.count, nsc, sv.cap, words, bits, bits + words, bits + 2 * words, perm, stats,
+                                c->stream), "particle ranks") || !read_stats())
+        return true;
+    if (st[1]) return false;
+    double* d8 = (double*)stage;
+    U* du = (U*)(d8 + 4 * chunk);
+    const ExportT<U> o{d8, d8 + chunk, d8 + 2 * chunk, (int64_t*)(d8 + 3 * chunk), du, du + chunk, du + 2 * chunk,
+                       du + 3 * chunk, (int32_t*)(du + 4 * chunk)};
+    for (int64_t r0 = 0; r0 < total; r0 += chunk) {
+        const int n = (int)std::min<int64_t>(chunk, total - r0);
+        auto out = [&](auto* host, const auto* dev) {
+            return run(hipMemcpyAsync(host + r0, dev, (size_t)n * sizeof *dev, hipMemcpyDeviceToHost, c->stream),
+                       "particle copy");
+        };
+        if (!run(launch_export_gather<R, U>(gview<R>(c), sv, perm, r0, n, o, c->stream), "particle gather") ||
+            !out(v->x, o.x) || !out(v->y, o.y) || !out(v->z, o.z) || !out(v->id, o.id) || !out(v->ux, o.ux) ||
+            !out(v->uy, o.uy) || !out(v->uz, o.uz) || !out(v->w, o.w) || (v->zstate && !out(v->zstate, o.zs)) ||
+            !run(hipStreamSynchronize(c->stream), "particle copy"))
+            return true;
+    }
+    rc = PIC_OK;
+    return true;
+}
+
 // Particle and field transfers, templated on the device real type R and the
 // host view (FP32 or FP64 momenta and weights).
 template <class R, class V>
@@ -494,6 +560,10 @@ int get_particles_t(pic_ctx* c, int s, V* v)
 {
     using U = typename std::remove_pointer<decltype(v->ux)>::type;
     const SpeciesViewT<R>& sv = sview<R>(c, s);
+    if (v->x && v->y && v->z && v->ux && v->uy && v->uz && v->w && v->id) {
+        int rc = PIC_OK;
+        if (export_particles<R>(c, s, v, rc)) return rc;
+    }
     std::vector<int32_t> cnt;
     const int64_t total = host_count(c, s, cnt);
     if (total < 0) return fail(c, PIC_ERR_HIP, "count readback failed");
@@ -826,7 +896,7 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
     g64.flags = g.flags;
     const size_t fbytes = (size_t)3 * N * (c->fp64 ? 8 : 4);
     void* fsp[3] = {};
-    c->fused = N <= FUSE_CELLS;
+    c->fused = N * (c->fp64 ? 8 : 4) <= FUSE_BYTES;
     for (void*& p : fsp)
         if (c->fused) fields_ok = fields_ok && (p = dev_alloc(c, fbytes));
     c->fs = FieldScratchT<float>{(float*)fsp[0], (float*)fsp[1], (float*)fsp[2]};

@@ -173,11 +173,11 @@ template <class R>
 hipError_t launch_yee_b(const GridViewT<R>& g, double coef, hipStream_t st);
 template <class R>
 hipError_t launch_yee_e(const GridViewT<R>& g, double coef, hipStream_t st);
-// The fused field update (k_fields.hip), for grids of up to FUSE_CELLS cells.
+// The fused field update (k_fields.hip), for grids whose field components take up to FUSE_BYTES each.
 // Scratch of 3 * N values each: the fields between its two kernels, and the
 // current accumulators the deposit adds to, zero between cycles (unused with
 // g.J64, whose sums are cleared the same way).
-constexpr int64_t FUSE_CELLS = 1 << 20;
+constexpr int64_t FUSE_BYTES = 3 << 20;
 template <class R>
 struct FieldScratchT {
     R *E, *B, *Jacc;
@@ -194,6 +194,25 @@ hipError_t launch_yee_head(const GridViewT<R>& g, const FieldScratchT<R>& f, dou
 template <class R>
 hipError_t launch_yee_tail(const GridViewT<R>& g, const FieldScratchT<R>& f, const MigrateArgsT<R>& mig,
                            double dt, hipStream_t st);
+
+// Particles in id order for the host (k_export.hip).  stats: {largest id,
+// duplicate ids seen, particles}, zero before the call.
+template <class U>
+struct ExportT {
+    double *x, *y, *z;
+    int64_t* id;
+    U *ux, *uy, *uz, *w;
+    int32_t* zs;
+};
+constexpr int EXPORT_CHUNK = 1 << 21;  // particles staged at a time
+hipError_t launch_export_stats(const uint32_t* id, const int32_t* count, int nsc, int cap, unsigned long long* stats,
+                               hipStream_t st);
+int64_t export_words(uint32_t id_max);  // words of the id bits
+hipError_t launch_export_rank(const uint32_t* id, const int32_t* count, int nsc, int cap, int64_t words, uint32_t* bits,
+                              uint32_t* before, uint32_t* block, uint32_t* perm, unsigned long long* stats, hipStream_t st);
+template <class R, class U>
+hipError_t launch_export_gather(const GridViewT<R>& g, const SpeciesViewT<R>& s, const uint32_t* perm, int64_t r0, int m,
+                                const ExportT<U>& o, hipStream_t st);
 
 // FP64 diagnostics.  partial buffers hold one entry per workgroup.
 struct DiagBuffers {
