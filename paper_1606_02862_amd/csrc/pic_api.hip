@@ -4,12 +4,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <limits>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -487,6 +489,35 @@ int64_t host_count(pic_ctx* c, int s, std::vector<int32_t>& counts)
     return t;
 }
 
+// Touches every page of the caller's output arrays from a few threads.  Fresh
+// arrays have no pages yet, and the copies that follow would fault them in one
+// by one on a single core (half of a 7 ms checkpoint of 0.9 M particles).
+struct PageToucher {
+    std::vector<std::thread> threads;
+    void start(const std::array<std::pair<char*, size_t>, 9>& spans)
+    {
+        size_t bytes = 0;
+        for (const auto& a : spans) bytes += a.second;
+        const unsigned cores = std::thread::hardware_concurrency();
+        const size_t n = std::min<size_t>({bytes >> 22, 8, cores ? cores : 1});  // a thread per 4 MiB
+        try {
+            for (size_t t = 0; t < n; ++t)
+                threads.emplace_back([=] {
+                    for (const auto& a : spans)
+                        for (size_t b = a.second / n * t, e = t + 1 == n ? a.second : a.second / n * (t + 1); b < e; b += 4096)
+                            *(volatile char*)(a.first + b) = 0;
+                });
+        } catch (...) {  // no thread or memory to spare: the copies fault the rest in
+        }
+    }
+    void join()
+    {
+        for (std::thread& t : threads) t.join();
+        threads.clear();
+    }
+    ~PageToucher() { join(); }
+};
+
 // The species' particles in id order by way of k_export.hip.  Returns false,
 // with rc untouched, where the host has to sort (duplicate or very sparse ids,
 // no device memory for the scratch); else true with rc the result.
@@ -529,10 +560,15 @@ bool export_particles(pic_ctx* c, int s, V* v, int& rc)
     uint32_t* perm = (uint32_t*)(m.p[2] = dev_alloc(c, (size_t)total * 4));
     char* stage = (char*)(m.p[3] = dev_alloc(c, (size_t)chunk * REC));
     if (!bits || !perm || !stage) return false;
+    PageToucher touch;  // beside the ranking
+    auto span = [&](auto* p) { return std::pair<char*, size_t>((char*)p, p ? (size_t)total * sizeof *p : 0); };
+    touch.start({{span(v->x), span(v->y), span(v->z), span(v->id), span(v->ux), span(v->uy), span(v->uz), span(v->w),
+                  span(v->zstate)}});
     if (!run(launch_export_rank(sv.id, sv.count, nsc, sv.cap, words, bits, bits + words, bits + 2 * words, perm, stats,
                                 c->stream), "particle ranks") || !read_stats())
         return true;
     if (st[1]) return false;
+    touch.join();
     double* d8 = (double*)stage;
     U* du = (U*)(d8 + 4 * chunk);
     const ExportT<U> o{d8, d8 + chunk, d8 + 2 * chunk, (int64_t*)(d8 + 3 * chunk), du, du + chunk, du + 2 * chunk,
