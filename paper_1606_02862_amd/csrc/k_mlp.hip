@@ -476,13 +476,25 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_moments(int64_t n, const double* 
     }
 }
 
-__global__ void k_mlp_moments_final(int64_t n, int nb, const double* partial, double* mu_s)
+// The partials added in order: wave 0 sums r, wave 1 r^2, from LDS (a single
+// thread that reads them from memory as it adds waits for each: 36 against 5 us).
+constexpr int MOM_BLOCKS = 512;
+__global__ __launch_bounds__(BLOCK) void k_mlp_moments_final(int64_t n, const double* partial, double* mu_s)
 {
+    __shared__ double p[2 * MOM_BLOCKS], sum[2];
+    for (int i = threadIdx.x; i < 2 * MOM_BLOCKS; i += BLOCK) p[i] = partial[i];
+    __syncthreads();
+    if (threadIdx.x == 0 || threadIdx.x == 64) {
+        const int k = threadIdx.x >> 6;
+        double a = 0.0;
+#pragma unroll 16
+        for (int i = 0; i < MOM_BLOCKS; ++i) a += p[2 * i + k];
+        sum[k] = a;
+    }
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    double a = 0.0, b = 0.0;
-    for (int i = 0; i < nb; ++i) { a += partial[2 * i]; b += partial[2 * i + 1]; }
-    const double mu = a / (double)n;
-    double var = b / (double)n - mu * mu;
+    const double mu = sum[0] / (double)n;
+    double var = sum[1] / (double)n - mu * mu;
     var = var > 1e-300 ? var : 1e-300;
     mu_s[0] = mu;
     mu_s[1] = sqrt(var);
@@ -496,9 +508,8 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_targets(int64_t n, const double* 
 
 hipError_t launch_mlp_standardize(int64_t n, const double* r, double* partial, double* mu_s, float* t, hipStream_t st)
 {
-    const int nb = 512;
-    hipLaunchKernelGGL(k_mlp_moments, dim3(nb), dim3(BLOCK), 0, st, n, r, partial);
-    hipLaunchKernelGGL(k_mlp_moments_final, dim3(1), dim3(64), 0, st, n, nb, partial, mu_s);
+    hipLaunchKernelGGL(k_mlp_moments, dim3(MOM_BLOCKS), dim3(BLOCK), 0, st, n, r, partial);
+    hipLaunchKernelGGL(k_mlp_moments_final, dim3(1), dim3(BLOCK), 0, st, n, partial, mu_s);
     hipLaunchKernelGGL(k_mlp_targets, dim3((unsigned)((n + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, st, n, r, mu_s, t);
     return hipGetLastError();
 }
@@ -529,7 +540,7 @@ hipError_t launch_mlp_init(uint64_t seed, float* P, float* m, float* v, hipStrea
 // Forward + backward of a minibatch.  Sample slot b of the batch is training
 // sample b (draw_seed == 0) or Philox (b, step, 4, 0) mod n_data.  Every wave
 // takes 16-sample tiles.  The block's gradient and squared-error sum (its
-// waves' partials added in wave order in LDS) go to row blockIdx.x of part
+// waves' partials added in wave order from LDS) go to row blockIdx.x of part
 // and lpart: no atomics, so the sums have a fixed order and training is
 // reproducible bit for bit.  (With one device-scope atomic add per wave and
 // parameter, those on one address queued behind each other beyond the L2 and
@@ -543,26 +554,69 @@ struct StepArgs {
     int64_t step;
 };
 
+// LDS rows of 64 BF16 values, padded to 72 (16-byte aligned, off the bank
+// period), and of the 16 samples of a tile, padded to 20 (8-byte aligned).
+constexpr int KP = NH + 8, SP = 16 + 4;
+
+// One wave's tile: its samples' features and targets, and the activations and
+// gradients that change lanes between the MFMAs.
+struct StepTile {
+    __bf16 h1T[NH][SP];   // H1 [unit][sample]
+    __bf16 dzT[NH][SP];   // dZ2 [unit][sample]
+    __bf16 dz[16][KP];    // dZ2 [sample][unit]
+    float x[16][NIN];
+    float t[16];
+};
+
+// What bounds a step is the latency of one wave's chain, 64 workgroups of a
+// 4096-sample batch being far fewer than the chip holds.  So each sample's
+// index is drawn once (not by every lane that needs one of its features), its
+// features and target are read once into LDS, the weights and the tiles that
+// feed MFMA operands lie in LDS as BF16 in operand order (one 8- or 16-byte
+// read per operand), and the waves' gradients are added by all lanes at once.
+// With 21 draws per lane, re-read features, FP32 tiles and the waves adding
+// one after another a step took 36 us. The arithmetic and its order are the
+// same, so are the results, bit for bit.
 template <int ACT>
 __global__ __launch_bounds__(BLOCK) void k_mlp_step(const float* P, StepArgs a, float* part, double* lpart)
 {
-    __shared__ float sW2[NH][NH + 1];                 // W2 (bf16-rounded), [out][in]
+    constexpr int NW = BLOCK / 64;
+    __shared__ __align__(16) __bf16 sW2[NH][KP], sW2T[NH][KP];  // W2 [out][in] and [in][out]
     __shared__ float sW1[NH][NIN], sB1[NH], sW3[NH];
-    // per-wave H1 tiles [sample][k] and dZ2 tiles [sample][n]; after the
-    // rounds, the block's gradient
-    __shared__ float tiles[2][BLOCK / 64][16][NH + 1];
-    auto& h1t = tiles[0];
-    auto& dz2t = tiles[1];
-    static_assert(sizeof(tiles) >= NPARAM * sizeof(float), "the block gradient fits the tiles");
-    __shared__ float gW1[BLOCK / 64][NH][NIN + 1];     // per-wave dW1 | db1
-    __shared__ double sL[BLOCK / 64];
+    __shared__ __align__(16) StepTile tiles[NW];
+    __shared__ float gW1[NW][NH][NIN + 1];   // per-wave dW1 | db1
+    __shared__ float grad[NW][NPARAM];       // per-wave gradients
+    __shared__ double sL[NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, c = lane & 15;
-    for (int i = tid; i < NH * NH; i += BLOCK) sW2[i / NH][i % NH] = bf16r(P[OFF_W2 + i]);
+    StepTile& T = tiles[wave];
+
+    // sample c of the tile: its index, then (group g) features 2g, 2g + 1 and the target
+    auto fetch = [&](int tile, float2& x, float& t) {
+        const int b = 16 * tile + c;
+        int64_t i = b;
+        if (a.draw_seed != 0) {
+            const Philox4 u = philox4x64_10((uint64_t)b, (uint64_t)a.step, PURPOSE_MLP_BATCH, 0, a.draw_seed, 0);
+            i = (int64_t)(u.v[0] % (uint64_t)a.n_data);
+        }
+        x = *reinterpret_cast<const float2*>(a.X + i * NIN + 2 * g);
+        t = a.t[i];
+    };
+    const int ntile = a.batch / 16;
+    const int nwave = gridDim.x * NW;
+    const int first = blockIdx.x * NW;
+    float2 xv{};
+    float tv = 0.0f;
+    if (first + wave < ntile) fetch(first + wave, xv, tv);  // in flight while the weights are staged
+
+    for (int i = tid; i < NH * NH; i += BLOCK) {
+        const __bf16 w = (__bf16)P[OFF_W2 + i];
+        sW2[i / NH][i % NH] = w;
+        sW2T[i % NH][i / NH] = w;
+    }
     for (int i = tid; i < NH * NIN; i += BLOCK) sW1[i / NIN][i % NIN] = bf16r(P[OFF_W1 + i]);
     for (int i = tid; i < NH; i += BLOCK) { sB1[i] = P[OFF_B1 + i]; sW3[i] = bf16r(P[OFF_W3 + i]); }
     for (int i = lane; i < NH * (NIN + 1); i += 64) gW1[wave][i / (NIN + 1)][i % (NIN + 1)] = 0.0f;
-    __syncthreads();
     const float b3 = P[OFF_B3];
     float b2v[4];
     for (int t = 0; t < 4; ++t) b2v[t] = P[OFF_B2 + 16 * t + c];
@@ -574,42 +628,37 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_step(const float* P, StepArgs a, 
     double lsum = 0.0;
     const float inv_b = 1.0f / (float)a.batch;
 
-    auto sample = [&](int b) -> int64_t {
-        if (a.draw_seed == 0) return b;
-        const Philox4 u = philox4x64_10((uint64_t)b, (uint64_t)a.step, PURPOSE_MLP_BATCH, 0, a.draw_seed, 0);
-        return (int64_t)(u.v[0] % (uint64_t)a.n_data);
-    };
-    const int ntile = a.batch / 16;
-    const int nwave = gridDim.x * (BLOCK / 64);
     // every wave of the block runs the same number of rounds (barriers inside)
-    for (int round = blockIdx.x * (BLOCK / 64); round < ntile; round += nwave) {
-        const int tile = round + wave;
-        const bool valid = tile < ntile;
-        bf16x8 h1[2];
-        float z2[4][4], dy[4];
+    for (int round = first; round < ntile; round += nwave) {
+        const bool valid = round + wave < ntile;
         if (valid) {
-            const int64_t si = sample(16 * tile + c);
+            T.x[c][2 * g] = xv.x;
+            T.x[c][2 * g + 1] = xv.y;
+            if (g == 0) T.t[c] = tv;
+        }
+        if (round + nwave + wave < ntile) fetch(round + nwave + wave, xv, tv);  // the next round's
+        __syncthreads();  // the tile (and before the first round the weights) in LDS
+        if (valid) {
             float x[NIN];
-            for (int k = 0; k < NIN; ++k) x[k] = a.X[si * NIN + k];
+            for (int k = 0; k < NIN; ++k) x[k] = T.x[c][k];
             // layer 1 for hidden units 32s + 8g + j of sample c
+            bf16x8 h1[2];
             for (int s = 0; s < 2; ++s)
                 for (int j = 0; j < 8; ++j) {
                     const int k = 32 * s + 8 * g + j;
                     float z = sB1[k];
                     for (int q = 0; q < NIN; ++q) z = fmaf(sW1[k][q], x[q], z);
-                    const float h = bf16r(act_f<ACT>(z));
-                    h1[s][j] = (__bf16)h;
-                    h1t[wave][c][k] = h;
+                    const __bf16 h = (__bf16)act_f<ACT>(z);
+                    h1[s][j] = h;
+                    T.h1T[k][c] = h;
                 }
             // layer 2 + head: rows i = 4g + r, columns n = 16t + c
-            float y[4] = {0.f, 0.f, 0.f, 0.f};
+            float z2[4][4], dy[4], y[4] = {0.f, 0.f, 0.f, 0.f};
             for (int t = 0; t < 4; ++t) {
-                bf16x8 w[2];
-                for (int s = 0; s < 2; ++s)
-                    for (int j = 0; j < 8; ++j) w[s][j] = (__bf16)sW2[16 * t + c][32 * s + 8 * g + j];
                 floatx4 d = {0.f, 0.f, 0.f, 0.f};
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1[0], w[0], d, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1[1], w[1], d, 0, 0, 0);
+                for (int s = 0; s < 2; ++s)
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        h1[s], *reinterpret_cast<const bf16x8*>(&sW2[16 * t + c][32 * s + 8 * g]), d, 0, 0, 0);
                 for (int r = 0; r < 4; ++r) {
                     z2[t][r] = d[r] + b2v[t];
                     y[r] = fmaf(sW3[16 * t + c], bf16r(act_f<ACT>(z2[t][r])), y[r]);
@@ -621,58 +670,56 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_step(const float* P, StepArgs a, 
                 v += __shfl_xor(v, 2, 64);
                 v += __shfl_xor(v, 4, 64);
                 v += __shfl_xor(v, 8, 64);
-                const int64_t so = sample(16 * tile + 4 * g + r);
-                const float res = v + b3 - a.t[so];
+                const float res = v + b3 - T.t[4 * g + r];
                 dy[r] = 2.0f * res * inv_b;
                 if (c == 0) lsum += (double)res * res;
             }
             // head and layer-2 backward: dZ2[i][n] = dy_i W3[n] act'(z2)
-            for (int t = 0; t < 4; ++t)
+            for (int t = 0; t < 4; ++t) {
+                bf16x4 dzv;
                 for (int r = 0; r < 4; ++r) {
                     const float h2 = bf16r(act_f<ACT>(z2[t][r]));
                     gW3[t] = fmaf(dy[r], h2, gW3[t]);
                     const float dz = dy[r] * sW3[16 * t + c] * dact_f<ACT>(z2[t][r]);
                     gB2[t] += dz;
-                    dz2t[wave][4 * g + r][16 * t + c] = dz;
+                    dzv[r] = (__bf16)dz;
+                    T.dz[4 * g + r][16 * t + c] = (__bf16)dz;
                 }
+                *reinterpret_cast<bf16x4*>(&T.dzT[16 * t + c][4 * g]) = dzv;
+            }
             for (int r = 0; r < 4; ++r) gB3 += (c == 0) ? dy[r] : 0.0f;
         }
-        __syncthreads();  // h1t / dz2t of this round complete
+        __syncthreads();  // the round's H1 and dZ2 complete
         if (valid) {
             // dW2[n][k] += sum_i dZ2[i][n] H1[i][k]: 16x16x16 MFMA, K = the 16 samples
+            bf16x4 h[4];
+            for (int tk = 0; tk < 4; ++tk) h[tk] = *reinterpret_cast<const bf16x4*>(&T.h1T[16 * tk + c][4 * g]);
             for (int tn = 0; tn < 4; ++tn) {
-                bf16x4 A;
-                for (int j = 0; j < 4; ++j) A[j] = (__bf16)dz2t[wave][4 * g + j][16 * tn + c];
-                for (int tk = 0; tk < 4; ++tk) {
-                    bf16x4 Bv;
-                    for (int j = 0; j < 4; ++j) Bv[j] = (__bf16)h1t[wave][4 * g + j][16 * tk + c];
-                    accW2[tn][tk] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, Bv, accW2[tn][tk], 0, 0, 0);
-                }
+                const bf16x4 A = *reinterpret_cast<const bf16x4*>(&T.dzT[16 * tn + c][4 * g]);
+                for (int tk = 0; tk < 4; ++tk)
+                    accW2[tn][tk] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, h[tk], accW2[tn][tk], 0, 0, 0);
             }
             // dH1[i][k] = sum_n dZ2[i][n] W2[n][k]: 16x16x32 MFMA over n; rows 4g + r, column 16tk + c
             bf16x8 dA[2];
-            for (int s = 0; s < 2; ++s)
-                for (int j = 0; j < 8; ++j) dA[s][j] = (__bf16)dz2t[wave][c][32 * s + 8 * g + j];
+            for (int s = 0; s < 2; ++s) dA[s] = *reinterpret_cast<const bf16x8*>(&T.dz[c][32 * s + 8 * g]);
+            float xs[4][NIN];
+            for (int r = 0; r < 4; ++r)
+                for (int q = 0; q < NIN; ++q) xs[r][q] = T.x[4 * g + r][q];
             for (int tk = 0; tk < 4; ++tk) {
-                bf16x8 Bv[2];
-                for (int s = 0; s < 2; ++s)
-                    for (int j = 0; j < 8; ++j) Bv[s][j] = (__bf16)sW2[32 * s + 8 * g + j][16 * tk + c];
                 floatx4 d = {0.f, 0.f, 0.f, 0.f};
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dA[0], Bv[0], d, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dA[1], Bv[1], d, 0, 0, 0);
+                for (int s = 0; s < 2; ++s)
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        dA[s], *reinterpret_cast<const bf16x8*>(&sW2T[16 * tk + c][32 * s + 8 * g]), d, 0, 0, 0);
                 // dZ1 = dH1 act'(z1) for samples 4g + r at unit k; dW1 / db1 partials
                 const int k = 16 * tk + c;
                 float part[NIN + 1];
                 for (int q = 0; q <= NIN; ++q) part[q] = 0.0f;
                 for (int r = 0; r < 4; ++r) {
-                    const int64_t so = sample(16 * tile + 4 * g + r);
-                    float xs[NIN];
-                    for (int q = 0; q < NIN; ++q) xs[q] = a.X[so * NIN + q];
                     float z1 = sB1[k];
-                    for (int q = 0; q < NIN; ++q) z1 = fmaf(sW1[k][q], xs[q], z1);
-                    const float dz1 = d[r] * dact_f<ACT>(z1);
-                    for (int q = 0; q < NIN; ++q) part[q] = fmaf(dz1, xs[q], part[q]);
-                    part[NIN] += dz1;
+                    for (int q = 0; q < NIN; ++q) z1 = fmaf(sW1[k][q], xs[r][q], z1);
+                    const float da = dact_f<ACT>(z1), dz1 = d[r] * da;
+                    for (int q = 0; q < NIN; ++q) part[q] = fmaf(dz1, xs[r][q], part[q]);
+                    part[NIN] = fmaf(d[r], da, part[NIN]);
                 }
                 // sum over the four row groups (lanes c, c+16, c+32, c+48); lane c owns the entry
                 for (int q = 0; q <= NIN; ++q) {
@@ -683,18 +730,29 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_step(const float* P, StepArgs a, 
                 }
             }
         }
-        __syncthreads();  // the next round overwrites h1t / dz2t
+        __syncthreads();  // the next round overwrites the tile
     }
-    // ---- the block's gradient: every wave's partial of every parameter, added
-    // in wave order (the tiles are free after the last round's barrier)
-    float* sG = &tiles[0][0][0][0];
-    float w3[4], b2[4];
+    // ---- every wave's gradient to LDS, then all lanes add the waves' in wave order
+    float* const G = grad[wave];
+#pragma unroll
+    for (int tn = 0; tn < 4; ++tn)
+#pragma unroll
+        for (int tk = 0; tk < 4; ++tk)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)  // D[m = n][nn = k]: row 16tn + 4g + r, column 16tk + c
+                G[OFF_W2 + (16 * tn + 4 * g + r) * NH + 16 * tk + c] = accW2[tn][tk][r];
+    for (int i = lane; i < NH * (NIN + 1); i += 64) {
+        const int k = i / (NIN + 1), q = i % (NIN + 1);
+        G[q < NIN ? OFF_W1 + k * NIN + q : OFF_B1 + k] = gW1[wave][k][q];
+    }
     for (int t = 0; t < 4; ++t) {
         float v = gW3[t], w = gB2[t];
         v += __shfl_xor(v, 16, 64); v += __shfl_xor(v, 32, 64);
         w += __shfl_xor(w, 16, 64); w += __shfl_xor(w, 32, 64);
-        w3[t] = v;
-        b2[t] = w;
+        if (g == 0) {
+            G[OFF_W3 + 16 * t + c] = v;
+            G[OFF_B2 + 16 * t + c] = w;
+        }
     }
     float b3s = gB3;
     double l = lsum;
@@ -702,69 +760,22 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_step(const float* P, StepArgs a, 
         b3s += __shfl_xor(b3s, o, 64);
         l += __shfl_xor(l, o, 64);
     }
-    // what this lane owns: 64 entries of W2, 9 of W1 | b1, with g == 0 the
-    // lane's 4 + 4 of W3 and b2, and lane 0 b3
-    constexpr int N1 = NH * (NIN + 1) / 64;
-    static_assert(NH * (NIN + 1) % 64 == 0, "W1 | b1 split evenly over the lanes");
-    int pos[64 + N1 + 8];
-    float val[64 + N1 + 8];
-#pragma unroll
-    for (int tn = 0; tn < 4; ++tn)
-#pragma unroll
-        for (int tk = 0; tk < 4; ++tk)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {  // D[m = n][nn = k]: row 16tn + 4g + r, column 16tk + c
-                pos[16 * tn + 4 * tk + r] = OFF_W2 + (16 * tn + 4 * g + r) * NH + 16 * tk + c;
-                val[16 * tn + 4 * tk + r] = accW2[tn][tk][r];
-            }
-#pragma unroll
-    for (int e = 0; e < N1; ++e) {
-        const int i = lane + 64 * e, k = i / (NIN + 1), q = i % (NIN + 1);
-        pos[64 + e] = q < NIN ? OFF_W1 + k * NIN + q : OFF_B1 + k;
-        val[64 + e] = gW1[wave][k][q];
+    if (lane == 0) {
+        G[OFF_B3] = b3s;
+        sL[wave] = l;
     }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        pos[64 + N1 + t] = OFF_W3 + 16 * t + c;
-        val[64 + N1 + t] = w3[t];
-        pos[64 + N1 + 4 + t] = OFF_B2 + 16 * t + c;
-        val[64 + N1 + 4 + t] = b2[t];
-    }
-    constexpr int NA = 64 + N1, NB = NA + 8;  // entries of every lane; of the g == 0 lanes
-    for (int w = 0; w < BLOCK / 64; ++w) {
-        if (wave == w) {
-            if (w > 0) {  // every load before the first store: one wait
-                float old[NB], old3 = 0.0f;
-#pragma unroll
-                for (int e = 0; e < NA; ++e) old[e] = sG[pos[e]];
-                if (g == 0)
-#pragma unroll
-                    for (int e = NA; e < NB; ++e) old[e] = sG[pos[e]];
-                if (lane == 0) old3 = sG[OFF_B3];
-#pragma unroll
-                for (int e = 0; e < NA; ++e) val[e] += old[e];
-                if (g == 0)
-#pragma unroll
-                    for (int e = NA; e < NB; ++e) val[e] += old[e];
-                b3s += old3;
-            }
-#pragma unroll
-            for (int e = 0; e < NA; ++e) sG[pos[e]] = val[e];
-            if (g == 0)
-#pragma unroll
-                for (int e = NA; e < NB; ++e) sG[pos[e]] = val[e];
-            if (lane == 0) {
-                sG[OFF_B3] = b3s;
-                sL[w] = l;
-            }
-        }
-        __syncthreads();
-    }
+    __syncthreads();
     float* row = part + (size_t)blockIdx.x * MLP_PART_STRIDE;
-    for (int i = tid; i < NPARAM; i += BLOCK) row[i] = sG[i];
+#pragma unroll 4
+    for (int i = tid; i < NPARAM; i += BLOCK) {
+        float v = grad[0][i];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += grad[w][i];
+        row[i] = v;
+    }
     if (tid == 0) {
         double ls = 0.0;
-        for (int w = 0; w < BLOCK / 64; ++w) ls += sL[w];
+        for (int w = 0; w < NW; ++w) ls += sL[w];
         lpart[blockIdx.x] = ls;
     }
 }
@@ -784,7 +795,7 @@ hipError_t launch_mlp_step(const float* P, const MlpStep& s, float* part, double
 // The summed gradient of parameter i: four lanes per parameter each add every
 // fourth row in row order, then two shuffle steps add the four sums.  With
 // ADAM, Adam on the FP32 master weights (beta1 0.9, beta2 0.999, eps 1e-8);
-// otherwise the sum goes to grad.  Thread 0 also sums the rows' squared errors.
+// otherwise the sum goes to grad.  The first wave also sums the rows' squared errors.
 template <bool ADAM>
 __global__ __launch_bounds__(BLOCK) void k_mlp_reduce(float* P, const float* part, int rows, const double* lpart,
                                                       double* loss, float* grad, float* m, float* v, float lr, float bc1,
@@ -794,15 +805,24 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_reduce(float* P, const float* par
     const int i = gid >> 2, j = gid & 3;
     float sum = 0.0f;
     if (i < NPARAM) {
-#pragma unroll 4
-        for (int r = j; r < rows; r += 4) sum += part[(size_t)r * MLP_PART_STRIDE + i];
+        if (rows == MLP_PART_ROWS) {  // every load in flight before the first add
+            float v[MLP_PART_ROWS / 4];
+#pragma unroll
+            for (int k = 0; k < MLP_PART_ROWS / 4; ++k) v[k] = part[(size_t)(4 * k + j) * MLP_PART_STRIDE + i];
+#pragma unroll
+            for (int k = 0; k < MLP_PART_ROWS / 4; ++k) sum += v[k];
+        } else {
+            for (int r = j; r < rows; r += 4) sum += part[(size_t)r * MLP_PART_STRIDE + i];
+        }
     }
     sum += __shfl_xor(sum, 1, 64);
     sum += __shfl_xor(sum, 2, 64);
-    if (gid == 0) {
+    if (gid < 64) {  // the first wave: one load of every row's, added in row order
+        static_assert(MLP_PART_ROWS <= 64, "a lane per row");
+        const double mine = gid < rows ? lpart[gid] : 0.0;
         double ls = 0.0;
-        for (int r = 0; r < rows; ++r) ls += lpart[r];
-        *loss = ls;
+        for (int r = 0; r < rows; ++r) ls += __shfl(mine, r, 64);
+        if (gid == 0) *loss = ls;
     }
     if (i >= NPARAM || j != 0) return;
     if constexpr (ADAM) {
