@@ -91,20 +91,41 @@ static_assert(sizeof(JAcc<float>) == 8 && sizeof(JAcc<double>) == 8, "8-byte cur
 // Separable interpolation of one staged component: sum_c wz sum_b wy sum_a wx f
 // over PX x PY x PZ nodes, f0 pointing at the component's first node (x
 // fastest in the tile of a shape of order ORDER).
+//
+// FP32 TSC (Tile::PAIRED) holds every node with its x-neighbour, (f_i, f_i+1).
+// The gather reads LDS at random nodes, where two adjacent values by
+// ds_read2_b32 cost 13.8 CU cycles per wave (7 for one) and an aligned
+// ds_read_b64 7.1: a row of three takes 14 instead of 20.  The doubled field
+// tile (40.7 KB, 77 KB in all) still lets two workgroups share a CU.
+// Measured: KHI 128^3 1.60 -> 1.48 ms per launch, 256x256x128 3.16 -> 2.97 ms.
 template <int ORDER, int PX, int PY, int PZ, class R>
 __device__ inline R interp_n(const R* f0, const R* wx, const R* wy, const R* wz)
 {
-    using T = Tile<ORDER>;
+    using T = Tile<ORDER, R>;
+    constexpr int FW = T::FW;
     R acc = R(0);
 #pragma unroll
     for (int c = 0; c < PZ; ++c) {
         R accy = R(0);
 #pragma unroll
         for (int b = 0; b < PY; ++b) {
-            const R* row = f0 + (c * T::GY + b) * T::GX;
+            const R* row = f0 + (c * T::GY + b) * T::GX * FW;
             R accx = R(0);
+            if constexpr (T::PAIRED) {
 #pragma unroll
-            for (int a = 0; a < PX; ++a) accx = rfma(wx[a], row[a], accx);
+                for (int a = 0; a < PX; a += 2) {
+                    if (a + 1 < PX) {
+                        const float2 v = *reinterpret_cast<const float2*>(row + 2 * a);
+                        accx = rfma(wx[a], v.x, accx);
+                        accx = rfma(wx[a + 1], v.y, accx);
+                    } else {
+                        accx = rfma(wx[a], row[2 * a], accx);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int a = 0; a < PX; ++a) accx = rfma(wx[a], row[a], accx);
+            }
             accy = rfma(wy[b], accx, accy);
         }
         acc = rfma(wz[c], accy, acc);
@@ -184,7 +205,7 @@ __device__ inline void flush_node(const GridView& g, int i, long long iv, float 
 // supercell, part p taking every parts-th frame from frame p.  Each stages the
 // fields and flushes a current tile of its own (the flush adds atomically
 // already); the supercell's hole list is shared, each part reserving its
-// range after its frame loop from a list of its own in LDS; the frames are
+// range after its frame loop from a list of its own; the frames are
 // dense when the kernel starts, since the field update's last kernel absorbs
 // the arrivals of every cycle.
 //
@@ -203,8 +224,9 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     constexpr bool STREAM = ORDER == 1 && std::is_same<R, float>::value;
     constexpr int JL = PCS ? PcsTile::JL : T::JL;
     __shared__ __align__(16) unsigned char smem[smem_bytes<ORDER, R>()];
-    R(*fE)[T::GN] = reinterpret_cast<R(*)[T::GN]>(smem);
-    R(*fB)[T::GN] = reinterpret_cast<R(*)[T::GN]>(smem + 3 * T::GN * RB);
+    constexpr int FW = T::FW, FN = T::GN * FW;  // values of a staged component
+    R(*fE)[FN] = reinterpret_cast<R(*)[FN]>(smem);
+    R(*fB)[FN] = reinterpret_cast<R(*)[FN]>(smem + 3 * FN * RB);
     R* const F = reinterpret_cast<R*>(smem);  // PCS: the six boxes at PcsTile::fbase
     A* tJ = reinterpret_cast<A*>(smem + jtile_offset<ORDER, R>());
     __shared__ int s_holes, s_queue, s_queue_m, s_cnt[3];
@@ -222,8 +244,9 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     const int part = SPLIT ? (int)blockIdx.x / g.nsc : 0;
     const int f0 = part * NT, fstep = SPLIT ? parts * NT : NT;
     const int sc = sc_of_block((int)blockIdx.x - part * g.nsc, g.nsc, g.ncx * g.ncy, g.xcd_remap);
-    __shared__ int s_left[SPLIT ? max_cap_in(ORDER) : 1];  // SPLIT: slots of this part's leavers
-    __shared__ int s_hbase;                                // and its range of the hole list
+    // SPLIT: slots of this part's leavers, and its range of the hole list
+    int32_t* const leavers = SPLIT ? s.left + (int64_t)blockIdx.x * s.cap_in : nullptr;
+    __shared__ int s_hbase;
     // arrivals of the previous step first (frames dense again before pushing)
     if (!SPLIT && apar >= 0) fill_supercell<NT>(g, s, sc, apar, reinterpret_cast<int*>(smem), s_cnt);
     const int tid = threadIdx.x;
@@ -249,8 +272,15 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
         } else {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                fE[c][t] = g.E[c * N + gi];
-                fB[c][t] = g.B[c * N + gi];
+                const R e = g.E[c * N + gi], b = g.B[c * N + gi];
+                fE[c][t * FW] = e;
+                fB[c][t * FW] = b;
+                if constexpr (T::PAIRED) {  // also the second of the pair before it
+                    if (t > 0) {
+                        fE[c][t * FW - 1] = e;
+                        fB[c][t * FW - 1] = b;
+                    }
+                }
             }
         }
     }
@@ -356,12 +386,12 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
             By = interp_n<ORDER, Q, P, Q>(&F[PcsTile::fbase(4) + bn + ox_ + oz_], wsx, wny, wsz) + g.b0y;
             Bz = interp_n<ORDER, Q, Q, P>(&F[PcsTile::fbase(5) + bn + ox_ + oy_], wsx, wsy, wnz) + g.b0z;
         } else {
-            Ex = interp_n<ORDER, Q, P, P>(&fE[0][bn + ox_], wsx, wny, wnz);
-            Ey = interp_n<ORDER, P, Q, P>(&fE[1][bn + oy_], wnx, wsy, wnz);
-            Ez = interp_n<ORDER, P, P, Q>(&fE[2][bn + oz_], wnx, wny, wsz);
-            Bx = interp_n<ORDER, P, Q, Q>(&fB[0][bn + oy_ + oz_], wnx, wsy, wsz) + g.b0x;
-            By = interp_n<ORDER, Q, P, Q>(&fB[1][bn + ox_ + oz_], wsx, wny, wsz) + g.b0y;
-            Bz = interp_n<ORDER, Q, Q, P>(&fB[2][bn + ox_ + oy_], wsx, wsy, wnz) + g.b0z;
+            Ex = interp_n<ORDER, Q, P, P>(&fE[0][(bn + ox_) * FW], wsx, wny, wnz);
+            Ey = interp_n<ORDER, P, Q, P>(&fE[1][(bn + oy_) * FW], wnx, wsy, wnz);
+            Ez = interp_n<ORDER, P, P, Q>(&fE[2][(bn + oz_) * FW], wnx, wny, wsz);
+            Bx = interp_n<ORDER, P, Q, Q>(&fB[0][(bn + oy_ + oz_) * FW], wnx, wsy, wsz) + g.b0x;
+            By = interp_n<ORDER, Q, P, Q>(&fB[1][(bn + ox_ + oz_) * FW], wsx, wny, wsz) + g.b0y;
+            Bz = interp_n<ORDER, Q, Q, P>(&fB[2][(bn + ox_ + oy_) * FW], wsx, wsy, wnz) + g.b0z;
         }
 
         // ---- relativistic Boris: half kick, rotation, half kick
@@ -490,7 +520,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
             const int hidx = hb + __popcll(lmask & ((1ull << lane) - 1ull));
             if (left) {
                 if (hidx < s.cap_in) {
-                    if constexpr (SPLIT) s_left[hidx] = slot;
+                    if constexpr (SPLIT) leavers[hidx] = slot;
                     else s.holes[(int64_t)sc * s.cap_in + hidx] = slot;
                 } else {
                     // hole list full (reported through FLAG_MIGRATE below): keep the
@@ -609,7 +639,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
         __syncthreads();
     }
     for (int t = tid; t < nh; t += NT) {
-        const int slot = SPLIT ? s_left[t] : s.holes[(int64_t)sc * s.cap_in + t];
+        const int slot = SPLIT ? leavers[t] : s.holes[(int64_t)sc * s.cap_in + t];
         const int64_t p = base + slot;
         if constexpr (SPLIT) {
             const int hidx = s_hbase + t;
@@ -749,7 +779,7 @@ hipError_t launch_push(const GridViewT<R>& g, const SpeciesViewT<R>& s, int orde
     // second frame, and a lane past the count stores into its own free slot
     if (s.cap % nt != 0 || s.cap > g.qcap || g.qcap % (nt / 64) != 0) return hipErrorInvalidValue;
     // SPLIT: dense frames, and room in a part's region of the queue for its share of full frames
-    if (parts < 0 || (parts > 0 && (apar >= 0 || g.qcap / parts < split_region(s.cap, parts)))) return hipErrorInvalidValue;
+    if (parts < 0 || (parts > 0 && (!s.left || parts > s.parts || apar >= 0 || g.qcap / parts < split_region(s.cap, parts)))) return hipErrorInvalidValue;
     if (s.cap_in > max_cap_in(order)) return hipErrorInvalidValue;
     R jscale = R(1), jinv = R(1);
     double jratio = 1.0;

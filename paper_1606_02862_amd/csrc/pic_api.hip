@@ -293,6 +293,11 @@ int alloc_species(pic_ctx* c, int s)
     }
     if (!(v.iid = (uint32_t*)dev_alloc(c, ni * 4))) return fail(c, PIC_ERR_OOM, "species %d: arrivals", s);
     if (!(v.holes = (int32_t*)dev_alloc(c, ni * 4))) return fail(c, PIC_ERR_OOM, "species %d: holes", s);
+    v.left = nullptr;
+    v.parts = c->fused ? split_parts(nsc, d.ppc > 0 ? d.ppc * SC_CELLS : v.cap, c->order) : 0;
+    c->split = c->split || v.parts > 0;
+    if (v.parts && !(v.left = (int32_t*)dev_alloc(c, (size_t)nsc * v.parts * cap_in * 4)))
+        return fail(c, PIC_ERR_OOM, "species %d: leavers", s);
     if (!(v.count = (int32_t*)dev_alloc(c, (size_t)nsc * 4))) return fail(c, PIC_ERR_OOM, "species %d: counts", s);
     if (!(v.in_count = (int32_t*)dev_alloc(c, (size_t)2 * nsc * 4))) return fail(c, PIC_ERR_OOM, "species %d: counts", s);
     if (!(v.hole_count = (int32_t*)dev_alloc(c, (size_t)nsc * 4))) return fail(c, PIC_ERR_OOM, "species %d: counts", s);
@@ -303,6 +308,7 @@ int alloc_species(pic_ctx* c, int s)
     w.id = v.id; w.zs = v.zs; w.count = v.count; w.cap = v.cap;
     w.iid = v.iid; w.izs = v.izs; w.in_count = v.in_count; w.holes = v.holes; w.hole_count = v.hole_count;
     w.cap_in = v.cap_in;
+    w.left = v.left; w.parts = v.parts;
     w.charge = d.charge;
     w.mass = d.mass;
     HIPCHK(c, launch_zero_i32(v.count, nsc, c->stream));
@@ -797,7 +803,7 @@ int step_t(pic_ctx* c, int n)
         for (int s = 0; s < c->nsp; ++s) {
             if (!c->sp[s].desc.mobile) continue;
             HIPCHK(c, launch_push<R>(gp, sview<R>(c, s), c->order, c->grid.gather == PIC_GATHER_GALERKIN,
-                                     push_vmax(c, s), jscale_g, apar, wpar, c->sp[s].parts, c->stream));
+                                     push_vmax(c, s), jscale_g, apar, wpar, c->sp[s].v.parts, c->stream));
             c->pending_launches += c->timing ? 1 : 0;
         }
         if (c->timing) HIPCHK(c, hipEventRecord(e1, c->stream));
@@ -983,10 +989,8 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
     // one deposit queue shared by the species (their particle kernels run one after another)
     g.qcap = 0;
     for (int s = 0; s < n_species; ++s) {
-        Species& S = c->sp[s];
-        S.parts = c->fused ? split_parts(g.nsc, S.desc.ppc > 0 ? S.desc.ppc * SC_CELLS : S.v.cap, c->order) : 0;
-        c->split = c->split || S.parts > 0;
-        g.qcap = std::max(g.qcap, S.parts ? S.parts * split_region(S.v.cap, S.parts) : S.v.cap);
+        const SpeciesView& v = c->sp[s].v;
+        g.qcap = std::max(g.qcap, v.parts ? v.parts * split_region(v.cap, v.parts) : v.cap);
     }
     g.qcap = (g.qcap + 511) / 512 * 512;  // whole 512-lane workgroups' worth of slots
     g64.qcap = g.qcap;

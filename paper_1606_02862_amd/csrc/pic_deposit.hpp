@@ -28,7 +28,10 @@ struct Tile {
     // LDS of the particle kernel: field tiles, then the current tile (one
     // 8-byte accumulator per node and component: int64 fixed point in FP32,
     // double in FP64) at a 16-byte aligned offset
-    static constexpr int FBYTES = (6 * GN * (int)sizeof(R) + 15) / 16 * 16;
+    // FP32 TSC keeps the fields as x-pairs (f_i, f_i+1), see interp_n
+    static constexpr bool PAIRED = ORDER == 2 && sizeof(R) == 4;
+    static constexpr int FW = PAIRED ? 2 : 1;  // values held per node
+    static constexpr int FBYTES = (6 * GN * FW * (int)sizeof(R) + 15) / 16 * 16;
     static constexpr int SMEM = FBYTES + 3 * JN * 8;
 };
 

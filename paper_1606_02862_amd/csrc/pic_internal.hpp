@@ -66,6 +66,8 @@ struct SpeciesViewT {
     int32_t* in_count;      // arrivals per parity and supercell (2 * nsc)
     int32_t* holes;         // per source supercell: vacated slots
     int32_t* hole_count;
+    int32_t* left;          // per part of a supercell: its leavers' slots (cap_in each), or nullptr
+    int parts;              // parts `left` has room for
     int cap_in;
     R charge;               // in e (per unit Z when zs != nullptr)
     R mass;
@@ -87,7 +89,6 @@ struct Species {
     pic_species_t desc;
     int64_t n_init;        // particles at t = 0
     int64_t id_offset;     // first id at t = 0
-    int parts;             // workgroups per supercell in the particle kernel (split_parts)
     double weight;
     double wmax;           // bound of |w| that sets the fixed-point current scale (>= wheld)
     double wheld;          // largest |w| known to be held (init, set, ionisation electrons)
