@@ -33,8 +33,9 @@ __device__ inline void moments_accumulate(const SpeciesView& e, int sc, MomLds& 
 #pragma unroll 4
     for (int t = tid; t < n; t += BLOCK) {
         const int64_t p = base + t;
-        const int cell = (int)ld(e.x[p]) + SX * ((int)ld(e.y[p]) + SY * (int)ld(e.z[p]));
-        const double w = ld(e.w[p]), ux = ld(e.ux[p]), uy = ld(e.uy[p]), uz = ld(e.uz[p]);
+        const float *r = e.pos + 3 * p, *u = e.mom + 3 * p;
+        const int cell = (int)ld(r[0]) + SX * ((int)ld(r[1]) + SY * (int)ld(r[2]));
+        const double w = ld(e.w[p]), ux = ld(u[0]), uy = ld(u[1]), uz = ld(u[2]);
         atomicAdd(&m.acc[0][cell], w);
         atomicAdd(&m.acc[1][cell], w * ux);
         atomicAdd(&m.acc[2][cell], w * uy);
@@ -93,7 +94,8 @@ struct PairLds {
 
 __device__ inline int ion_cell(const SpeciesView& ion, int64_t p)
 {
-    return (int)ion.x[p] + SX * ((int)ion.y[p] + SY * (int)ion.z[p]);
+    const Triple<float> r = ld3(ion.pos, p);
+    return (int)r.x + SX * ((int)r.y + SY * (int)r.z);
 }
 
 // Marks the pairs of the supercell's ions (and keeps every ion's cell in
@@ -225,8 +227,8 @@ __device__ inline int append_events(const SpeciesView& ion, const SpeciesView& e
         }
         const int64_t q = (int64_t)sc * el.cap + ebase + kk;
         const int znew = Z0 + e + 1;
-        el.x[q] = ion.x[p]; el.y[q] = ion.y[p]; el.z[q] = ion.z[p];
-        el.ux[q] = ion.ux[p]; el.uy[q] = ion.uy[p]; el.uz[q] = ion.uz[p];
+        st3(el.pos, q, ld3(ion.pos, p));
+        st3(el.mom, q, ld3(ion.mom, p));
         el.w[q] = ion.w[p];
         el.id[q] = (uint32_t)(a.id_base_new + (int64_t)(id - (uint32_t)a.ion_id_offset) * tab.z_max + (znew - 1));
         dE += tab.P[Z0 + e];

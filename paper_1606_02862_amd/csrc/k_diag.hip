@@ -111,7 +111,8 @@ __global__ __launch_bounds__(BLOCK) void k_kinetic(GridViewT<R> g, SpeciesViewT<
     const int64_t base = (int64_t)sc * s.cap;
     double acc = 0.0;
     for (int t = threadIdx.x; t < n; t += BLOCK) {
-        const double ux = s.ux[base + t], uy = s.uy[base + t], uz = s.uz[base + t];
+        const Triple<R> u = ld3(s.mom, base + t);
+        const double ux = u.x, uy = u.y, uz = u.z;
         const double u2 = ux * ux + uy * uy + uz * uz;
         acc += (double)s.w[base + t] * (u2 / (1.0 + sqrt(1.0 + u2)));  // gamma - 1
     }
@@ -184,9 +185,10 @@ __global__ __launch_bounds__(BLOCK) void k_rho(GridViewT<R> g, SpeciesViewT<R> s
         const double qw = q * (double)s.w[p] * inv_dv;
         int fx, fy, fz;
         double wx[4], wy[4], wz[4];
-        rho_weights<ORDER>((double)s.x[p], &fx, wx);
-        rho_weights<ORDER>((double)s.y[p], &fy, wy);
-        rho_weights<ORDER>((double)s.z[p], &fz, wz);
+        const Triple<R> r = ld3(s.pos, p);
+        rho_weights<ORDER>((double)r.x, &fx, wx);
+        rho_weights<ORDER>((double)r.y, &fy, wy);
+        rho_weights<ORDER>((double)r.z, &fz, wz);
         // a particle inside its supercell always passes; anything else is skipped
         if (fx < -1 || fx > SX + 1 - ORDER || fy < -1 || fy > SY + 1 - ORDER || fz < -1 || fz > SZ + 1 - ORDER) continue;
 #pragma unroll

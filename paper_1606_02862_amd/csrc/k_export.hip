@@ -123,12 +123,13 @@ __global__ __launch_bounds__(BLOCK) void k_export_gather(GridViewT<R> g, Species
     const uint32_t p = perm[r0 + i];
     const int sc = (int)(p / (uint32_t)s.cap);
     const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
-    o.x[i] = (double)(scx * SX) + (double)s.x[p];
-    o.y[i] = (double)(scy * SY) + (double)s.y[p];
-    o.z[i] = (double)(scz * SZ) + (double)s.z[p];
-    o.ux[i] = (U)s.ux[p];
-    o.uy[i] = (U)s.uy[p];
-    o.uz[i] = (U)s.uz[p];
+    const Triple<R> r = ld3(s.pos, p), u = ld3(s.mom, p);
+    o.x[i] = (double)(scx * SX) + (double)r.x;
+    o.y[i] = (double)(scy * SY) + (double)r.y;
+    o.z[i] = (double)(scz * SZ) + (double)r.z;
+    o.ux[i] = (U)u.x;
+    o.uy[i] = (U)u.y;
+    o.uz[i] = (U)u.z;
     o.w[i] = (U)s.w[p];
     o.id[i] = (int64_t)s.id[p];
     o.zs[i] = s.zs ? (int32_t)s.zs[p] : 0;

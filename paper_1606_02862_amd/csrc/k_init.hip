@@ -46,12 +46,9 @@ __global__ __launch_bounds__(BLOCK) void k_init_species(GridViewT<R> g, SpeciesV
         if (a.layout == PIC_LAYOUT_SHEAR) sign = (4 * j >= g.ny && 4 * j < 3 * g.ny) ? 1.0 : -1.0;
         if (a.layout == PIC_LAYOUT_BEAMS) sign = (slot % 2 == 0) ? 1.0 : -1.0;
         const int64_t p = base + (int64_t)slot * BLOCK + c;
-        s.x[p] = x;
-        s.y[p] = y;
-        s.z[p] = z;
-        s.ux[p] = (R)(sign * drift[0] + uth * n0);
-        s.uy[p] = (R)(sign * drift[1] + uth * n1);
-        s.uz[p] = (R)(sign * drift[2] + uth * n2);
+        st3(s.pos, p, Triple<R>{x, y, z});
+        st3(s.mom, p, Triple<R>{(R)(sign * drift[0] + uth * n0), (R)(sign * drift[1] + uth * n1),
+                                (R)(sign * drift[2] + uth * n2)});
         s.w[p] = (R)a.weight;
         s.id[p] = (uint32_t)myid;
         if (s.zs) s.zs[p] = (uint8_t)a.z_init;

@@ -339,8 +339,9 @@ __global__ __launch_bounds__(BLOCK) void k_energy_loss(GridView g, SpeciesView e
     const int scx = sc % g.ncx, scy = (sc / g.ncx) % g.ncy, scz = sc / (g.ncx * g.ncy);
     for (int t = threadIdx.x; t < n; t += BLOCK) {
         const int64_t p = base + t;
-        const int64_t gi = (int64_t)(scx * SX + (int)el.x[p]) +
-                           (int64_t)g.nx * ((scy * SY + (int)el.y[p]) + (int64_t)g.ny * (scz * SZ + (int)el.z[p]));
+        const Triple<float> r = ld3(el.pos, p);
+        const int64_t gi = (int64_t)(scx * SX + (int)r.x) +
+                           (int64_t)g.nx * ((scy * SY + (int)r.y) + (int64_t)g.ny * (scz * SZ + (int)r.z));
         const double d = db.de[gi];
         if (!(d > 0.0)) continue;
         const double heat = 1.5 * db.mom4[4 * gi] * db.kT[gi];
@@ -348,9 +349,9 @@ __global__ __launch_bounds__(BLOCK) void k_energy_loss(GridView g, SpeciesView e
         const double f2 = 1.0 - d / heat;
         const double f = f2 > 0.0 ? sqrt(f2) : 0.0;
         const double bx = db.mom4[4 * gi + 1], by = db.mom4[4 * gi + 2], bz = db.mom4[4 * gi + 3];
-        el.ux[p] = (float)(bx + f * ((double)el.ux[p] - bx));
-        el.uy[p] = (float)(by + f * ((double)el.uy[p] - by));
-        el.uz[p] = (float)(bz + f * ((double)el.uz[p] - bz));
+        const Triple<float> u = ld3(el.mom, p);
+        st3(el.mom, p, Triple<float>{(float)(bx + f * ((double)u.x - bx)), (float)(by + f * ((double)u.y - by)),
+                                     (float)(bz + f * ((double)u.z - bz))});
     }
 }
 

@@ -184,6 +184,27 @@ __device__ inline void st_part(E* base, unsigned byte_off, E v)
     else at(base, byte_off) = v;
 }
 
+// Triples (FP32) of the frame loop with the non-temporal hint: the hint keeps
+// the compiler from merging three scalar accesses, so the 12-byte buffer
+// instructions are named.  `rs` spans the slab's triples.
+using f32x3 = float __attribute__((ext_vector_type(3)));
+using u32x3 = unsigned __attribute__((ext_vector_type(3)));
+__device__ inline __amdgpu_buffer_rsrc_t slab_rsrc(float* p, int cap)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, cap * 12, 0x00027000);
+}
+constexpr int AUX_NT = 2;
+__device__ inline Triple<float> ld3_stream(__amdgpu_buffer_rsrc_t rs, unsigned byte_off)
+{
+    const f32x3 v = __builtin_bit_cast(f32x3, __builtin_amdgcn_raw_buffer_load_b96(rs, byte_off, 0, AUX_NT));
+    return Triple<float>{v.x, v.y, v.z};
+}
+__device__ inline void st3_stream(__amdgpu_buffer_rsrc_t rs, unsigned byte_off, float x, float y, float z)
+{
+    const f32x3 v = {x, y, z};
+    __builtin_amdgcn_raw_buffer_store_b96(__builtin_bit_cast(u32x3, v), rs, byte_off, 0, AUX_NT);
+}
+
 // Add one node of a supercell's fixed-point current tile to global J: as an
 // FP32 atomic, or (PIC_OPT_DETERMINISTIC_J) rescaled to the cycle's common
 // scale (jratio <= 1, rounded to nearest) and added to the 64-bit fixed-point
@@ -306,12 +327,13 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     bool bad = false;
 
     // this supercell's frames: block-uniform base pointers, 32-bit slot offsets
-    R* const px = s.x + base;
-    R* const py = s.y + base;
-    R* const pz = s.z + base;
-    R* const pux = s.ux + base;
-    R* const puy = s.uy + base;
-    R* const puz = s.uz + base;
+    R* const ppos = s.pos + 3 * base;
+    R* const pmom = s.mom + 3 * base;
+    [[maybe_unused]] __amdgpu_buffer_rsrc_t rpos, rmom;
+    if constexpr (STREAM) {
+        rpos = slab_rsrc(ppos, s.cap);
+        rmom = slab_rsrc(pmom, s.cap);
+    }
     const R* const pw = s.w + base;
     const uint8_t* const pzs = HAS_Z ? s.zs + base : nullptr;
 
@@ -331,8 +353,16 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     auto load_part = [&](int sl) {
         const unsigned un = RB * (unsigned)sl;
         Part p;
-        p.x = ld_part<STREAM>(px, un); p.y = ld_part<STREAM>(py, un); p.z = ld_part<STREAM>(pz, un);
-        p.ux = ld_part<STREAM>(pux, un); p.uy = ld_part<STREAM>(puy, un); p.uz = ld_part<STREAM>(puz, un);
+        Triple<R> r, u;
+        if constexpr (STREAM) {
+            r = ld3_stream(rpos, 3 * un);
+            u = ld3_stream(rmom, 3 * un);
+        } else {
+            r = Triple<R>{at(ppos, 3 * un), at(ppos, 3 * un + RB), at(ppos, 3 * un + 2 * RB)};
+            u = Triple<R>{at(pmom, 3 * un), at(pmom, 3 * un + RB), at(pmom, 3 * un + 2 * RB)};
+        }
+        p.x = r.x; p.y = r.y; p.z = r.z;
+        p.ux = u.x; p.uy = u.y; p.uz = u.z;
         p.w = ld_part<STREAM>(pw, un);
         p.zs = 0;
         if constexpr (HAS_Z) p.zs = pzs[sl];
@@ -357,7 +387,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     // body on a copy of the last particle; it deposits and queues nothing, is
     // never a leaver and only stores into its own free slot (slot < cap)
     auto push_one = [&](const int slot, const Part& pp, const bool valid) {
-        const unsigned u = RB * (unsigned)slot;  // byte offset of the slot
+        const unsigned u = 3 * RB * (unsigned)slot;  // byte offset of the slot's triples
         const R x0 = pp.x, y0 = pp.y, z0 = pp.z;
         const R ux0 = pp.ux, uy0 = pp.uy, uz0 = pp.uz;
         const R wgt = pp.w;
@@ -506,8 +536,13 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
         // ---- store in place; a particle that left the supercell keeps its
         // unshifted position here and its slot goes on the hole list, handed
         // over after the frame loop so no wave waits on a global atomic here
-        st_part<STREAM>(px, u, x1); st_part<STREAM>(py, u, y1); st_part<STREAM>(pz, u, z1);
-        st_part<STREAM>(pux, u, ux); st_part<STREAM>(puy, u, uy); st_part<STREAM>(puz, u, uz);
+        if constexpr (STREAM) {
+            st3_stream(rpos, u, x1, y1, z1);
+            st3_stream(rmom, u, ux, uy, uz);
+        } else {
+            at(ppos, u) = x1; at(ppos, u + RB) = y1; at(ppos, u + 2 * RB) = z1;
+            at(pmom, u) = ux; at(pmom, u + RB) = uy; at(pmom, u + 2 * RB) = uz;
+        }
         const bool left = valid && ((x1 < R(0)) || (x1 >= (R)SX) || (y1 < R(0)) || (y1 >= (R)SY) ||
                                     (z1 < R(0)) || (z1 >= (R)SZ));
         const unsigned long long lmask = __ballot(left);
@@ -525,9 +560,9 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
                 } else {
                     // hole list full (reported through FLAG_MIGRATE below): keep the
                     // particle inside its supercell so every later access stays in bounds
-                    at(px, u) = rmin(rmax(x1, R(0)), xm);
-                    at(py, u) = rmin(rmax(y1, R(0)), ym);
-                    at(pz, u) = rmin(rmax(z1, R(0)), zm);
+                    at(ppos, u) = rmin(rmax(x1, R(0)), xm);
+                    at(ppos, u + RB) = rmin(rmax(y1, R(0)), ym);
+                    at(ppos, u + 2 * RB) = rmin(rmax(z1, R(0)), zm);
                 }
             }
         }
@@ -539,7 +574,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
             pb = load_part(NT + tid < n ? NT + tid : n - 1);
             // set A has arrived, set B stays in flight: the loop's waits then
             // count the steady state's loads and stores, not this prologue's
-            constexpr int LOADS = HAS_Z ? 8 : 7;
+            constexpr int LOADS = HAS_Z ? 4 : 3;
             __builtin_amdgcn_s_waitcnt(0x0F70 | LOADS);  // vmcnt(LOADS)
         }
     }
@@ -646,15 +681,14 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
             if (hidx < s.cap_in) {
                 s.holes[(int64_t)sc * s.cap_in + hidx] = slot;
             } else {  // the parts together overflow the list: as for one part above
-                s.x[p] = rmin(rmax(s.x[p], R(0)), xm);
-                s.y[p] = rmin(rmax(s.y[p], R(0)), ym);
-                s.z[p] = rmin(rmax(s.z[p], R(0)), zm);
+                const Triple<R> r = ld3(s.pos, p);
+                st3(s.pos, p, Triple<R>{rmin(rmax(r.x, R(0)), xm), rmin(rmax(r.y, R(0)), ym), rmin(rmax(r.z, R(0)), zm)});
                 g.flags[FLAG_MIGRATE] = 1;
                 continue;
             }
         }
-        const R x1 = s.x[p], y1 = s.y[p], z1 = s.z[p];
-        const R lux = s.ux[p], luy = s.uy[p], luz = s.uz[p], lw = s.w[p];
+        const Triple<R> lr = ld3(s.pos, p), lu = ld3(s.mom, p);
+        const R x1 = lr.x, y1 = lr.y, z1 = lr.z, lw = s.w[p];
         const uint32_t lid = s.id[p];
         const uint8_t lzs = HAS_Z ? s.zs[p] : (uint8_t)0;
         const int mvx = (x1 < R(0)) ? -1 : (x1 >= (R)SX ? 1 : 0);
@@ -690,12 +724,11 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
         if (k < s.cap_in) {
             const int64_t q_ = inbox_index(s, g.nsc, wpar, dest, k);
             // shift into the destination's frame; x - (-8) can round up onto the far face
-            s.ix[q_] = rmin(x1 - (R)(mvx * SX), xm);
-            s.iy[q_] = rmin(y1 - (R)(mvy * SY), ym);
-            s.iz[q_] = rmin(z1 - (R)(mvz * SZ), zm);
-            s.iux[q_] = lux; s.iuy[q_] = luy; s.iuz[q_] = luz;
-            s.iw[q_] = lw;
-            s.iid[q_] = lid;
+            s.in[2 * q_] = make4(rmin(x1 - (R)(mvx * SX), xm), rmin(y1 - (R)(mvy * SY), ym),
+                                 rmin(z1 - (R)(mvz * SZ), zm), lw);
+            R idv;
+            put_id(idv, lid);
+            s.in[2 * q_ + 1] = make4(lu.x, lu.y, lu.z, idv);
             if constexpr (HAS_Z) s.izs[q_] = lzs;
         } else {
             g.flags[FLAG_MIGRATE] = 1;

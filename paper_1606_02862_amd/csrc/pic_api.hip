@@ -248,12 +248,11 @@ int validate(const pic_grid_t* g, const pic_species_t* sp, int n, pic_shape_t sh
 template <class R>
 int alloc_real_arrays(pic_ctx* c, int s, SpeciesViewT<R>& v, size_t n, size_t ni)
 {
-    R** fl[] = {&v.x, &v.y, &v.z, &v.ux, &v.uy, &v.uz, &v.w};
-    for (R** f : fl)
-        if (!(*f = (R*)dev_alloc(c, n * sizeof(R)))) return fail(c, PIC_ERR_OOM, "species %d: frames", s);
-    R** fi[] = {&v.ix, &v.iy, &v.iz, &v.iux, &v.iuy, &v.iuz, &v.iw};
-    for (R** f : fi)
-        if (!(*f = (R*)dev_alloc(c, ni * sizeof(R)))) return fail(c, PIC_ERR_OOM, "species %d: arrivals", s);
+    if (!(v.pos = (R*)dev_alloc(c, 3 * n * sizeof(R))) || !(v.mom = (R*)dev_alloc(c, 3 * n * sizeof(R))) ||
+        !(v.w = (R*)dev_alloc(c, n * sizeof(R))))
+        return fail(c, PIC_ERR_OOM, "species %d: frames", s);
+    using R4 = typename Vec4<R>::type;
+    if (!(v.in = (R4*)dev_alloc(c, 2 * ni * sizeof(R4)))) return fail(c, PIC_ERR_OOM, "species %d: arrivals", s);
     return PIC_OK;
 }
 
@@ -291,7 +290,6 @@ int alloc_species(pic_ctx* c, int s)
         if (!(v.zs = (uint8_t*)dev_alloc(c, n))) return fail(c, PIC_ERR_OOM, "species %d: charge states", s);
         if (!(v.izs = (uint8_t*)dev_alloc(c, ni))) return fail(c, PIC_ERR_OOM, "species %d: arrivals", s);
     }
-    if (!(v.iid = (uint32_t*)dev_alloc(c, ni * 4))) return fail(c, PIC_ERR_OOM, "species %d: arrivals", s);
     if (!(v.holes = (int32_t*)dev_alloc(c, ni * 4))) return fail(c, PIC_ERR_OOM, "species %d: holes", s);
     v.left = nullptr;
     v.parts = c->fused ? split_parts(nsc, d.ppc > 0 ? d.ppc * SC_CELLS : v.cap, c->order) : 0;
@@ -306,7 +304,7 @@ int alloc_species(pic_ctx* c, int s)
     // the FP64 view shares every integer array and size
     SpeciesView64& w = S.v64;
     w.id = v.id; w.zs = v.zs; w.count = v.count; w.cap = v.cap;
-    w.iid = v.iid; w.izs = v.izs; w.in_count = v.in_count; w.holes = v.holes; w.hole_count = v.hole_count;
+    w.izs = v.izs; w.in_count = v.in_count; w.holes = v.holes; w.hole_count = v.hole_count;
     w.cap_in = v.cap_in;
     w.left = v.left; w.parts = v.parts;
     w.charge = d.charge;
@@ -614,12 +612,10 @@ int get_particles_t(pic_ctx* c, int s, V* v)
         return fail(c, PIC_ERR_ARG, "view arrays must not be NULL");
     if (v->capacity < total) return fail(c, PIC_ERR_ARG, "view capacity %lld < %lld particles", (long long)v->capacity, (long long)total);
     const size_t n = (size_t)c->g.nsc * sv.cap;
-    std::vector<R> a[7];
-    const R* src[7] = {sv.x, sv.y, sv.z, sv.ux, sv.uy, sv.uz, sv.w};
-    for (int k = 0; k < 7; ++k) {
-        a[k].resize(n);
-        HIPCHK(c, hipMemcpyAsync(a[k].data(), src[k], n * sizeof(R), hipMemcpyDeviceToHost, c->stream));
-    }
+    std::vector<R> pos(3 * n), mom(3 * n), w(n);
+    HIPCHK(c, hipMemcpyAsync(pos.data(), sv.pos, 3 * n * sizeof(R), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(mom.data(), sv.mom, 3 * n * sizeof(R), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(w.data(), sv.w, n * sizeof(R), hipMemcpyDeviceToHost, c->stream));
     std::vector<uint32_t> ids(n);
     std::vector<uint8_t> zs;
     HIPCHK(c, hipMemcpyAsync(ids.data(), sv.id, n * 4, hipMemcpyDeviceToHost, c->stream));
@@ -637,13 +633,13 @@ int get_particles_t(pic_ctx* c, int s, V* v)
         const size_t p = order[k];
         const int sc = (int)(p / sv.cap);
         const int scx = sc % c->g.ncx, scy = (sc / c->g.ncx) % c->g.ncy, scz = sc / (c->g.ncx * c->g.ncy);
-        v->x[k] = (double)(scx * SX) + (double)a[0][p];
-        v->y[k] = (double)(scy * SY) + (double)a[1][p];
-        v->z[k] = (double)(scz * SZ) + (double)a[2][p];
-        v->ux[k] = (U)a[3][p];
-        v->uy[k] = (U)a[4][p];
-        v->uz[k] = (U)a[5][p];
-        v->w[k] = (U)a[6][p];
+        v->x[k] = (double)(scx * SX) + (double)pos[3 * p];
+        v->y[k] = (double)(scy * SY) + (double)pos[3 * p + 1];
+        v->z[k] = (double)(scz * SZ) + (double)pos[3 * p + 2];
+        v->ux[k] = (U)mom[3 * p];
+        v->uy[k] = (U)mom[3 * p + 1];
+        v->uz[k] = (U)mom[3 * p + 2];
+        v->w[k] = (U)w[p];
         v->id[k] = ids[p];
         if (v->zstate) v->zstate[k] = sv.zs ? zs[p] : 0;
     }
@@ -660,8 +656,7 @@ int set_particles_t(pic_ctx* c, int s, const V* v)
     const GridView& g = c->g;
     const size_t n = (size_t)g.nsc * sv.cap;
     std::vector<int32_t> cnt(g.nsc, 0);
-    std::vector<R> a[7];
-    for (auto& x : a) x.assign(n, R(0));
+    std::vector<R> pos(3 * n, R(0)), mom(3 * n, R(0)), w(n, R(0));
     std::vector<uint32_t> ids(n, 0);
     std::vector<uint8_t> zs(sv.zs ? n : 0, 0);
     const R lim[3] = {face_below<R>((R)SX), face_below<R>((R)SY), face_below<R>((R)SZ)};
@@ -689,8 +684,11 @@ int set_particles_t(pic_ctx* c, int s, const V* v)
         if (cnt[sc] >= sv.cap) return fail(c, PIC_ERR_CAPACITY, "supercell %d holds more than %d particles", sc, sv.cap);
         wmax = std::max(wmax, std::fabs(u[3]));
         const size_t q = (size_t)sc * sv.cap + cnt[sc]++;
-        a[0][q] = rel[0]; a[1][q] = rel[1]; a[2][q] = rel[2];
-        a[3][q] = (R)u[0]; a[4][q] = (R)u[1]; a[5][q] = (R)u[2]; a[6][q] = (R)u[3];
+        for (int d = 0; d < 3; ++d) {
+            pos[3 * q + d] = rel[d];
+            mom[3 * q + d] = (R)u[d];
+        }
+        w[q] = (R)u[3];
         ids[q] = (uint32_t)v->id[k];
         if (sv.zs) {
             const int z = v->zstate ? v->zstate[k] : c->sp[s].desc.z_init;
@@ -698,9 +696,9 @@ int set_particles_t(pic_ctx* c, int s, const V* v)
             zs[q] = (uint8_t)z;
         }
     }
-    R* dst[7] = {sv.x, sv.y, sv.z, sv.ux, sv.uy, sv.uz, sv.w};
-    for (int k = 0; k < 7; ++k)
-        HIPCHK(c, hipMemcpyAsync(dst[k], a[k].data(), n * sizeof(R), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(sv.pos, pos.data(), 3 * n * sizeof(R), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(sv.mom, mom.data(), 3 * n * sizeof(R), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(sv.w, w.data(), n * sizeof(R), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(sv.id, ids.data(), n * 4, hipMemcpyHostToDevice, c->stream));
     if (sv.zs) HIPCHK(c, hipMemcpyAsync(sv.zs, zs.data(), n, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(sv.count, cnt.data(), (size_t)g.nsc * 4, hipMemcpyHostToDevice, c->stream));

@@ -71,6 +71,24 @@ __device__ inline double rrcp(double x) { return 1.0 / x; }
 __device__ inline float4 make4(float a, float b, float c, float d) { return make_float4(a, b, c, d); }
 __device__ inline double4 make4(double a, double b, double c, double d) { return make_double4(a, b, c, d); }
 
+// A position or momentum triple of slot p (one 12- or 24-byte access).
+template <class R>
+struct Triple {
+    R x, y, z;
+};
+template <class R> __device__ inline Triple<R> ld3(const R* a, int64_t p) { return Triple<R>{a[3 * p], a[3 * p + 1], a[3 * p + 2]}; }
+template <class R> __device__ inline void st3(R* a, int64_t p, const Triple<R>& t)
+{
+    a[3 * p] = t.x;
+    a[3 * p + 1] = t.y;
+    a[3 * p + 2] = t.z;
+}
+// An id as the fourth value of an arrival record, and back.
+__device__ inline void put_id(float& d, uint32_t id) { d = __uint_as_float(id); }
+__device__ inline void put_id(double& d, uint32_t id) { d = __longlong_as_double((long long)id); }
+__device__ inline uint32_t get_id(float d) { return __float_as_uint(d); }
+__device__ inline uint32_t get_id(double d) { return (uint32_t)__double_as_longlong(d); }
+
 // ---------------------------------------------------------------- shapes
 // NGP (order 0, used by the Galerkin gather): node floor(x + 1/2), weight 1.
 // CIC: nodes f, f+1 with f = floor(x); weights 1-d, d (d = x - f).

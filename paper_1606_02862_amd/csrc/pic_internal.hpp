@@ -52,16 +52,20 @@ struct GridViewT {
 
 template <class R>
 struct SpeciesViewT {
-    R *x, *y, *z;           // supercell-relative positions in cells: [0,8)x[0,8)x[0,4)
-    R *ux, *uy, *uz;        // u = gamma v
+    // Positions and momenta as triples (element 3 p + d of slot p): one access
+    // of 3 values moves a particle's position, at the stream's full rate when
+    // the lanes take consecutive slots, and a migrating particle touches 2
+    // lines instead of 6.
+    R* pos;                 // supercell-relative, in cells: [0,8)x[0,8)x[0,4)
+    R* mom;                 // u = gamma v
     R* w;                   // macro weight
     uint32_t* id;
     uint8_t* zs;            // charge state, or nullptr
     int32_t* count;         // particles per supercell
     int cap;                // slots per supercell (multiple of 256)
-    // arrival lists: per step parity and destination supercell, cap_in slots
-    R *ix, *iy, *iz, *iux, *iuy, *iuz, *iw;
-    uint32_t* iid;
+    // arrival lists: per step parity and destination supercell, cap_in slots of
+    // two records {x, y, z, w}, {ux, uy, uz, id (its bits)}
+    typename Vec4<R>::type* in;
     uint8_t* izs;
     int32_t* in_count;      // arrivals per parity and supercell (2 * nsc)
     int32_t* holes;         // per source supercell: vacated slots

@@ -49,14 +49,12 @@ __device__ inline int fill_supercell(const GridViewT<R>& g, const SpeciesViewT<R
         np = s.cap;
     }
     // the first NT arrivals, loaded while the holes are classified
-    R pfx = R(0), pfy = R(0), pfz = R(0), pfux = R(0), pfuy = R(0), pfuz = R(0), pfw = R(0);
-    uint32_t pfid = 0;
+    using R4 = typename Vec4<R>::type;
+    R4 pf0{}, pf1{};
     uint8_t pfzs = 0;
     if (tid < m) {
         const int64_t q = inbox_index(s, g.nsc, par, sc, tid);
-        pfx = s.ix[q]; pfy = s.iy[q]; pfz = s.iz[q];
-        pfux = s.iux[q]; pfuy = s.iuy[q]; pfuz = s.iuz[q];
-        pfw = s.iw[q]; pfid = s.iid[q];
+        pf0 = s.in[2 * q]; pf1 = s.in[2 * q + 1];
         if (s.zs) pfzs = s.izs[q];
     }
     const int lo = np < n ? np : n;  // survivors at or above n' must move down
@@ -91,25 +89,23 @@ __device__ inline int fill_supercell(const GridViewT<R>& g, const SpeciesViewT<R
     for (int t = tid; t < nsv; t += NT) {  // survivors
         const int64_t d = base + s_vac[t];
         const int64_t q = base + s_src[t];
-        s.x[d] = s.x[q]; s.y[d] = s.y[q]; s.z[d] = s.z[q];
-        s.ux[d] = s.ux[q]; s.uy[d] = s.uy[q]; s.uz[d] = s.uz[q];
+        st3(s.pos, d, ld3(s.pos, q));
+        st3(s.mom, d, ld3(s.mom, q));
         s.w[d] = s.w[q]; s.id[d] = s.id[q];
         if (s.zs) s.zs[d] = s.zs[q];
     }
     for (int a = tid; a < nmove - nsv; a += NT) {  // arrival a into vacancy nsv + a
         const int64_t d = base + s_vac[nsv + a];
-        if (a == tid) {
-            s.x[d] = pfx; s.y[d] = pfy; s.z[d] = pfz;
-            s.ux[d] = pfux; s.uy[d] = pfuy; s.uz[d] = pfuz;
-            s.w[d] = pfw; s.id[d] = pfid;
-            if (s.zs) s.zs[d] = pfzs;
-        } else {
+        if (a != tid) {
             const int64_t q = inbox_index(s, g.nsc, par, sc, a);
-            s.x[d] = s.ix[q]; s.y[d] = s.iy[q]; s.z[d] = s.iz[q];
-            s.ux[d] = s.iux[q]; s.uy[d] = s.iuy[q]; s.uz[d] = s.iuz[q];
-            s.w[d] = s.iw[q]; s.id[d] = s.iid[q];
-            if (s.zs) s.zs[d] = s.izs[q];
+            pf0 = s.in[2 * q]; pf1 = s.in[2 * q + 1];
+            if (s.zs) pfzs = s.izs[q];
         }
+        st3(s.pos, d, Triple<R>{pf0.x, pf0.y, pf0.z});
+        st3(s.mom, d, Triple<R>{pf1.x, pf1.y, pf1.z});
+        s.w[d] = pf0.w;
+        s.id[d] = get_id(pf1.w);
+        if (s.zs) s.zs[d] = pfzs;
     }
     __syncthreads();  // moves visible to the whole workgroup; scratch free again
     if (tid == 0) {
