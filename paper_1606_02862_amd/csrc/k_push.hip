@@ -228,15 +228,27 @@ __device__ inline void flush_node(const GridView& g, int i, long long iv, float 
 // already); the supercell's hole list is shared, each part reserving its
 // range after its frame loop from a list of its own; the frames are
 // dense when the kernel starts, since the field update's last kernel absorbs
-// the arrivals of every cycle.
+// the arrivals of every cycle.  One launch takes every species with the same
+// template arguments, so that the workgroups of all fill the chip together.
+// Measured, two species: CIC 56x40x28, 8 per cell, deterministic, four cycles
+// 194 -> 153 us; TSC on 125 to 250 supercells 1.3x faster.
 //
 // Waves per SIMD the register budget is fitted to: 4 in FP32, 2 in FP64.
 template <class R> constexpr int push_waves() { return std::is_same<R, float>::value ? 4 : 2; }
 
 template <int ORDER, bool HAS_Z, bool GAL, int NT, class R, bool SPLIT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(push_waves<R>())))
-void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, int apar, int wpar, int parts)
+void k_push(GridViewT<R> g, PushArgsT<R> args, int apar, int wpar)
 {
+    // the species of this workgroup (block-uniform); one in the default variant
+    int sp = 0;
+    if constexpr (SPLIT)
+        while (sp + 1 < args.n && (int)blockIdx.x >= args.sp[sp + 1].first) ++sp;
+    const PushSpeciesT<R>& ps = args.sp[SPLIT ? sp : 0];
+    const SpeciesViewT<R>& s = ps.s;
+    const R jscale = ps.jscale, jinv = ps.jinv;
+    const double jratio = ps.jratio;
+    const int parts = ps.parts, blk = (int)blockIdx.x - (SPLIT ? ps.first : 0);
     using T = Tile<ORDER, R>;
     using A = JAcc<R>;
     using R4 = typename Vec4<R>::type;
@@ -262,11 +274,11 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
     __shared__ int s_qn[NW], s_qo[NW];
 
     // SPLIT: this part's frames begin at f0 and advance by fstep
-    const int part = SPLIT ? (int)blockIdx.x / g.nsc : 0;
+    const int part = SPLIT ? blk / g.nsc : 0;
     const int f0 = part * NT, fstep = SPLIT ? parts * NT : NT;
-    const int sc = sc_of_block((int)blockIdx.x - part * g.nsc, g.nsc, g.ncx * g.ncy, g.xcd_remap);
+    const int sc = sc_of_block(blk - part * g.nsc, g.nsc, g.ncx * g.ncy, g.xcd_remap);
     // SPLIT: slots of this part's leavers, and its range of the hole list
-    int32_t* const leavers = SPLIT ? s.left + (int64_t)blockIdx.x * s.cap_in : nullptr;
+    int32_t* const leavers = SPLIT ? s.left + (int64_t)blk * s.cap_in : nullptr;
     __shared__ int s_hbase;
     // arrivals of the previous step first (frames dense again before pushing)
     if (!SPLIT && apar >= 0) fill_supercell<NT>(g, s, sc, apar, reinterpret_cast<int*>(smem), s_cnt);
@@ -316,7 +328,7 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
 
     const int n = s.count[sc];
     const int64_t base = (int64_t)sc * s.cap;
-    const int64_t qbase = (int64_t)sc * g.qcap + part * qreg;
+    const int64_t qbase = (int64_t)(sp * g.nsc + sc) * g.qcap + part * qreg;  // (species of one launch: a queue each)
     const R dt = g.dt;
     const R cdx = dt / g.dx, cdy = dt / g.dy, cdz = dt / g.dz;
     const R inv_dvdt = R(1) / (g.dx * g.dy * g.dz * dt);
@@ -785,14 +797,11 @@ void k_push(GridViewT<R> g, SpeciesViewT<R> s, R jscale, R jinv, double jratio, 
 }
 
 template <int ORDER, int NT, class R, bool SPLIT>
-static void launch_push_order(const GridViewT<R>& g, const SpeciesViewT<R>& s, bool gal, R jscale, R jinv,
-                              double jratio, int apar, int wpar, int parts, hipStream_t st)
+static void launch_push_order(const GridViewT<R>& g, const PushArgsT<R>& a, bool gal, int apar, int wpar, int blocks,
+                              hipStream_t st)
 {
-    const dim3 grid(g.nsc * (SPLIT ? parts : 1)), block(NT);
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, st, g, s, jscale, jinv, jratio, apar, wpar, parts);
-    };
-    const bool hz = s.zs != nullptr;
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(NT), 0, st, g, a, apar, wpar); };
+    const bool hz = a.sp[0].s.zs != nullptr;
     if (gal) {
         if (hz) go(k_push<ORDER, true, true, NT, R, SPLIT>);
         else go(k_push<ORDER, false, true, NT, R, SPLIT>);
@@ -803,46 +812,61 @@ static void launch_push_order(const GridViewT<R>& g, const SpeciesViewT<R>& s, b
 }
 
 template <class R>
-hipError_t launch_push(const GridViewT<R>& g, const SpeciesViewT<R>& s, int order, bool galerkin, double vmax,
-                       float jscale_g, int apar, int wpar, int parts, hipStream_t st)
+hipError_t launch_push(const GridViewT<R>& g, const PushItemT<R>* items, int n, int order, bool galerkin,
+                       float jscale_g, int apar, int wpar, hipStream_t st)
 {
     // the deposit queue holds a full supercell, split evenly over the waves of a workgroup
     const int nt = order == 1 ? 256 : 512;
-    // whole frames per slab: the paired frame loop runs every lane of a pair's
-    // second frame, and a lane past the count stores into its own free slot
-    if (s.cap % nt != 0 || s.cap > g.qcap || g.qcap % (nt / 64) != 0) return hipErrorInvalidValue;
-    // SPLIT: dense frames, and room in a part's region of the queue for its share of full frames
-    if (parts < 0 || (parts > 0 && (!s.left || parts > s.parts || apar >= 0 || g.qcap / parts < split_region(s.cap, parts)))) return hipErrorInvalidValue;
-    if (s.cap_in > max_cap_in(order)) return hipErrorInvalidValue;
-    R jscale = R(1), jinv = R(1);
-    double jratio = 1.0;
-    if constexpr (std::is_same<R, float>::value) {
-        // fixed-point scale: one contribution is at most vmax in magnitude -> |int| <= 2^30
-        jscale = fixed_scale(vmax);
-        jinv = 1.0f / jscale;
-        // the common scale of the deterministic J is never finer than the species' own
-        if (g.J64) {
-            if (!(jscale_g > 0.0f) || jscale_g > jscale) return hipErrorInvalidValue;
-            jratio = (double)jscale_g / (double)jscale;
+    const bool split = n > 0 && items[0].parts > 0;
+    if (n < 1 || n > PIC_MAX_SPECIES || (n > 1 && !split)) return hipErrorInvalidValue;
+    PushArgsT<R> a{};
+    a.n = n;
+    int blocks = 0;
+    for (int k = 0; k < n; ++k) {
+        const SpeciesViewT<R>& s = *items[k].s;
+        int parts = items[k].parts;
+        // whole frames per slab: the paired frame loop runs every lane of a pair's
+        // second frame, and a lane past the count stores into its own free slot
+        if (s.cap % nt != 0 || s.cap > g.qcap || g.qcap % (nt / 64) != 0) return hipErrorInvalidValue;
+        if (s.cap_in > max_cap_in(order) || (s.zs != nullptr) != (items[0].s->zs != nullptr)) return hipErrorInvalidValue;
+        // SPLIT: dense frames, and room in a part's region of the queue for its share of full frames
+        if ((parts > 0) != split) return hipErrorInvalidValue;
+        if (split && (!s.left || parts > s.parts || apar >= 0 || g.qcap / parts < split_region(s.cap, parts)))
+            return hipErrorInvalidValue;
+        PushSpeciesT<R>& p = a.sp[k];
+        p.s = s;
+        p.jscale = p.jinv = R(1);
+        p.jratio = 1.0;
+        if constexpr (std::is_same<R, float>::value) {
+            // fixed-point scale: one contribution is at most vmax in magnitude -> |int| <= 2^30
+            p.jscale = fixed_scale(items[k].vmax);
+            p.jinv = 1.0f / p.jscale;
+            // the common scale of the deterministic J is never finer than the species' own
+            if (g.J64) {
+                if (!(jscale_g > 0.0f) || jscale_g > p.jscale) return hipErrorInvalidValue;
+                p.jratio = (double)jscale_g / (double)p.jscale;
+            }
         }
+        // a tile rescaled to the common scale is rounded once per node: order-independent only as one tile per supercell
+        if (parts > 1 && p.jratio != 1.0) parts = 1;
+        p.parts = split ? parts : 1;
+        p.first = blocks;
+        blocks += g.nsc * p.parts;
     }
-    // a tile rescaled to the common scale is rounded once per node: order-independent only as one tile per supercell
-    if (parts > 1 && jratio != 1.0) parts = 1;
-    if (parts > 0) {
-        if (order == 1) launch_push_order<1, SPLIT_NT, R, true>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, parts, st);
-        else if (order == 2) launch_push_order<2, SPLIT_NT, R, true>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, parts, st);
-        else launch_push_order<3, SPLIT_NT, R, true>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, parts, st);
+    if (split) {
+        if (order == 1) launch_push_order<1, SPLIT_NT, R, true>(g, a, galerkin, apar, wpar, blocks, st);
+        else if (order == 2) launch_push_order<2, SPLIT_NT, R, true>(g, a, galerkin, apar, wpar, blocks, st);
+        else launch_push_order<3, SPLIT_NT, R, true>(g, a, galerkin, apar, wpar, blocks, st);
     } else {
-        if (order == 1) launch_push_order<1, 256, R, false>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, 1, st);
-        else if (order == 2) launch_push_order<2, 512, R, false>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, 1, st);
-        else launch_push_order<3, 512, R, false>(g, s, galerkin, jscale, jinv, jratio, apar, wpar, 1, st);
+        if (order == 1) launch_push_order<1, 256, R, false>(g, a, galerkin, apar, wpar, blocks, st);
+        else if (order == 2) launch_push_order<2, 512, R, false>(g, a, galerkin, apar, wpar, blocks, st);
+        else launch_push_order<3, 512, R, false>(g, a, galerkin, apar, wpar, blocks, st);
     }
     return hipGetLastError();
 }
 
-template hipError_t launch_push<float>(const GridView&, const SpeciesView&, int, bool, double, float, int, int,
-                                       int, hipStream_t);
-template hipError_t launch_push<double>(const GridView64&, const SpeciesView64&, int, bool, double, float, int, int,
-                                        int, hipStream_t);
+template hipError_t launch_push<float>(const GridView&, const PushItemT<float>*, int, int, bool, float, int, int, hipStream_t);
+template hipError_t launch_push<double>(const GridView64&, const PushItemT<double>*, int, int, bool, float, int, int,
+                                        hipStream_t);
 
 }  // namespace pic

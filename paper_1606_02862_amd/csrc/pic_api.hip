@@ -266,16 +266,31 @@ template <class R> SpeciesViewT<R>& sview(pic_ctx* c, int s);
 template <> SpeciesView& sview<float>(pic_ctx* c, int s) { return c->sp[s].v; }
 template <> SpeciesView64& sview<double>(pic_ctx* c, int s) { return c->sp[s].v64; }
 
+// Slots per supercell of a species.
+int slab_cap(const pic_ctx* c, const pic_species_t& d)
+{
+    int cap_ppc = d.cap_ppc > 0 ? d.cap_ppc : (d.ppc * 3 + 1) / 2;
+    if (cap_ppc < 1) cap_ppc = 1;
+    if (c->order >= 2) cap_ppc += cap_ppc & 1;  // whole 512-particle frames per supercell
+    return cap_ppc * SC_CELLS;
+}
+
+// The mobile species that share species s's launch of the split particle kernel.
+int launch_species(const pic_ctx* c, int s)
+{
+    int n = 0;
+    for (int t = 0; t < c->nsp; ++t)
+        n += c->sp[t].desc.mobile && (c->sp[t].desc.z_max > 0) == (c->sp[s].desc.z_max > 0);
+    return n < 1 ? 1 : n;
+}
+
 int alloc_species(pic_ctx* c, int s)
 {
     Species& S = c->sp[s];
     SpeciesView& v = S.v;
     const pic_species_t& d = S.desc;
     const int nsc = c->g.nsc;
-    int cap_ppc = d.cap_ppc > 0 ? d.cap_ppc : (d.ppc * 3 + 1) / 2;
-    if (cap_ppc < 1) cap_ppc = 1;
-    if (c->order >= 2) cap_ppc += cap_ppc & 1;  // whole 512-particle frames per supercell
-    v.cap = cap_ppc * SC_CELLS;
+    v.cap = slab_cap(c, d);
     int cap_in = v.cap / 4;
     cap_in = std::max(cap_in, 256);
     cap_in = std::min(cap_in, c->order == 1 ? 2048 : MAX_MIGRATE);  // what the particle kernel's LDS can absorb
@@ -292,8 +307,6 @@ int alloc_species(pic_ctx* c, int s)
     }
     if (!(v.holes = (int32_t*)dev_alloc(c, ni * 4))) return fail(c, PIC_ERR_OOM, "species %d: holes", s);
     v.left = nullptr;
-    v.parts = c->fused ? split_parts(nsc, d.ppc > 0 ? d.ppc * SC_CELLS : v.cap, c->order) : 0;
-    c->split = c->split || v.parts > 0;
     if (v.parts && !(v.left = (int32_t*)dev_alloc(c, (size_t)nsc * v.parts * cap_in * 4)))
         return fail(c, PIC_ERR_OOM, "species %d: leavers", s);
     if (!(v.count = (int32_t*)dev_alloc(c, (size_t)nsc * 4))) return fail(c, PIC_ERR_OOM, "species %d: counts", s);
@@ -798,11 +811,25 @@ int step_t(pic_ctx* c, int n)
         // step `it` writes its leavers to parity it & 1 and absorbs the previous step's
         // (split: every step's arrivals are absorbed at its end instead)
         const int wpar = it & 1, apar = it > 0 && !c->split ? ((it - 1) & 1) : -1;
-        for (int s = 0; s < c->nsp; ++s) {
-            if (!c->sp[s].desc.mobile) continue;
-            HIPCHK(c, launch_push<R>(gp, sview<R>(c, s), c->order, c->grid.gather == PIC_GATHER_GALERKIN,
-                                     push_vmax(c, s), jscale_g, apar, wpar, c->sp[s].v.parts, c->stream));
-            c->pending_launches += c->timing ? 1 : 0;
+        // one launch per species, or (split) per group of species with and without charge states
+        for (int z = 0; z < 2; ++z) {
+            PushItemT<R> items[PIC_MAX_SPECIES];
+            int n_items = 0;
+            auto flush = [&]() -> hipError_t {
+                const hipError_t e = n_items ? launch_push<R>(gp, items, n_items, c->order,
+                                                              c->grid.gather == PIC_GATHER_GALERKIN, jscale_g, apar,
+                                                              wpar, c->stream)
+                                             : hipSuccess;
+                c->pending_launches += c->timing ? n_items : 0;
+                n_items = 0;
+                return e;
+            };
+            for (int s = 0; s < c->nsp; ++s) {
+                if (!c->sp[s].desc.mobile || (c->sp[s].desc.z_max > 0) != (z == 1)) continue;
+                items[n_items++] = PushItemT<R>{&sview<R>(c, s), push_vmax(c, s), c->sp[s].v.parts};
+                if (!c->split) HIPCHK(c, flush());
+            }
+            HIPCHK(c, flush());
         }
         if (c->timing) HIPCHK(c, hipEventRecord(e1, c->stream));
         const bool last = it == n - 1;  // of the call: leave the frames dense, keep J
@@ -981,19 +1008,29 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
         S.wheld = S.weight;
         off += S.n_init;
     }
+    for (int s = 0; s < n_species && c->fused; ++s) {
+        const pic_species_t& d = c->sp[s].desc;
+        const int n = d.ppc > 0 ? d.ppc * SC_CELLS : slab_cap(c, d);
+        c->sp[s].v.parts = split_parts(g.nsc, n, c->order, launch_species(c, s));
+        c->split = c->split || (d.mobile && c->sp[s].v.parts > 0);
+    }
     for (int s = 0; s < n_species; ++s) {
         if ((rc = alloc_species(c, s))) return bail(rc);
     }
-    // one deposit queue shared by the species (their particle kernels run one after another)
+    // one deposit queue shared by the species whose particle kernels run one after
+    // another, one for each species of a shared launch
     g.qcap = 0;
+    int queues = 1;
     for (int s = 0; s < n_species; ++s) {
         const SpeciesView& v = c->sp[s].v;
         g.qcap = std::max(g.qcap, v.parts ? v.parts * split_region(v.cap, v.parts) : v.cap);
+        if (c->split) queues = std::max(queues, launch_species(c, s));
     }
     g.qcap = (g.qcap + 511) / 512 * 512;  // whole 512-lane workgroups' worth of slots
     g64.qcap = g.qcap;
-    const bool q_ok = c->fp64 ? (g64.qbuf = (double4*)dev_alloc(c, (size_t)2 * g.nsc * g.qcap * sizeof(double4))) != nullptr
-                              : (g.qbuf = (float4*)dev_alloc(c, (size_t)2 * g.nsc * g.qcap * sizeof(float4))) != nullptr;
+    const size_t nq = (size_t)2 * queues * g.nsc * g.qcap;
+    const bool q_ok = c->fp64 ? (g64.qbuf = (double4*)dev_alloc(c, nq * sizeof(double4))) != nullptr
+                              : (g.qbuf = (float4*)dev_alloc(c, nq * sizeof(float4))) != nullptr;
     if (!q_ok) {
         c->err = "device allocation of the deposit queue failed";
         return bail(PIC_ERR_OOM);

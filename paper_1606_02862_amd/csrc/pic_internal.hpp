@@ -41,7 +41,7 @@ struct GridViewT {
     R* B;
     R* J;
     int32_t* flags;        // NFLAGS, in pinned host memory (kernels store to it on an error only)
-    typename Vec4<R>::type* qbuf;  // deposit queue: nsc * qcap records of 2 (x0,y0,z0,qw | x1,y1,z1,-)
+    typename Vec4<R>::type* qbuf;  // deposit queue (one per species of a launch): nsc * qcap records of 2 (x0,y0,z0,qw | x1,y1,z1,-)
     int qcap;              // queue slots per supercell (>= every species' frame capacity, in whole frames of a part)
     // PIC_OPT_DETERMINISTIC_J (FP32): 3 * N int64 fixed-point current at the
     // cycle's common scale, which the field update converts (times jinv64) into
@@ -124,17 +124,38 @@ hipError_t launch_zero_f64(double* p, int64_t n, hipStream_t st);
 hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st);
 inline hipError_t launch_zero_r(float* p, int64_t n, hipStream_t st) { return launch_zero_f32(p, n, st); }
 inline hipError_t launch_zero_r(double* p, int64_t n, hipStream_t st) { return launch_zero_f64(p, n, st); }
+// The species of one particle-kernel launch: one, or with parts > 0 (the split
+// variant) several that agree in having charge states or not.
 // vmax: upper bound of |q w| max(dx,dy,dz) / (dV dt) over the species' particles
+// parts: 0 for one workgroup per supercell; else the workgroups of SPLIT_NT
+// lanes that share one (the arrivals then absorbed before the launch, apar = -1)
 // apar: parity of the arrivals to absorb first (-1: none); wpar: parity the
 // leavers of this step are written to
 // galerkin: the reduced-order gather along staggered axes (PIC_GATHER_GALERKIN)
 // jscale_g: with g.J64, the cycle's common fixed-point scale (2^30 over the
 // largest vmax of the cycle's species); each tile is rescaled to it at the flush
-// parts: 0 for one workgroup per supercell; else the workgroups of SPLIT_NT
-// lanes that share one (the arrivals then absorbed before the launch, apar = -1)
 template <class R>
-hipError_t launch_push(const GridViewT<R>& g, const SpeciesViewT<R>& s, int order, bool galerkin, double vmax,
-                       float jscale_g, int apar, int wpar, int parts, hipStream_t st);
+struct PushItemT {
+    const SpeciesViewT<R>* s;
+    double vmax;
+    int parts;
+};
+template <class R>
+hipError_t launch_push(const GridViewT<R>& g, const PushItemT<R>* items, int n, int order, bool galerkin,
+                       float jscale_g, int apar, int wpar, hipStream_t st);
+// The same as the kernel takes it: the fixed-point scales, and each species' first block.
+template <class R>
+struct PushSpeciesT {
+    SpeciesViewT<R> s;
+    R jscale, jinv;
+    double jratio;
+    int parts, first;
+};
+template <class R>
+struct PushArgsT {
+    PushSpeciesT<R> sp[PIC_MAX_SPECIES];
+    int n;
+};
 constexpr int SPLIT_NT = 512;
 // Queue slots a part needs: its share of a full slab, in whole frames.
 inline int split_region(int cap, int parts)
@@ -142,18 +163,19 @@ inline int split_region(int cap, int parts)
     const int per = SPLIT_NT * parts;
     return (cap + per - 1) / per * SPLIT_NT;
 }
-// The parts of a supercell of a species with about n particles per supercell,
-// 0 for the default variant.  Up to 512 supercells: the number that makes the
-// fullest CU's work least, its workgroups (of 256 CUs) times the frames of
-// each plus 3 for the staging, clearing and flush of a tile (fitted to the
-// figures below).  One part is the default's work on 512 lanes, better than its
-// 256 for CIC only.  Measured, two cycles with 16 particles per cell (default
+// The parts of a supercell of a species with about n particles per supercell
+// (one of nsp that share a launch), 0 for the default variant.  Up to 512
+// supercells: the number that makes the fullest CU's work least, its workgroups
+// (of 256 CUs) times the frames of each plus 3 for the staging, clearing and
+// flush of a tile (fitted to the figures below).  One part is the default's
+// work on 512 lanes, better than its 256 for CIC, or for species that share a
+// launch.  Measured, two cycles with 16 particles per cell (default
 // against 1, 2, 4, 8 parts; us):
 //   TSC  16 supercells 155 / 74 (8), 125: 164 / 126 (2), 130 (4), 152 (8),
 //        256: 176 / 178 (1), 203 (4), 384: 275 / 279 (1), 240 (2), 640: 374 / 384 (1);
 //   CIC  64 supercells 97 / 64 (4), 70 (8), 256: 107 / 96 (1), 640: 165 / 176 (1);
 // with 4 per cell TSC 384: 118 / 118 (1), 136 (2).
-inline int split_parts(int nsc, int n, int order)
+inline int split_parts(int nsc, int n, int order, int nsp)
 {
     constexpr int CUS = 256, TILE = 3;
     if (nsc > 2 * CUS) return 0;
@@ -161,10 +183,10 @@ inline int split_parts(int nsc, int n, int order)
     int best = 1;
     int64_t least = INT64_MAX;
     for (int p = 1; p <= frames && (int64_t)nsc * p <= 4 * CUS; ++p) {
-        const int64_t cost = ((int64_t)nsc * p + CUS - 1) / CUS * (TILE + (frames + p - 1) / p);
+        const int64_t cost = ((int64_t)nsc * nsp * p + CUS - 1) / CUS * (TILE + (frames + p - 1) / p);
         if (cost < least) { least = cost; best = p; }
     }
-    return best == 1 && order > 1 ? 0 : best;
+    return best == 1 && order > 1 && nsp == 1 ? 0 : best;
 }
 // Fixed-point scale of a current tile: 2^30 over the bound vmax of one contribution.
 inline float fixed_scale(double vmax)

@@ -81,3 +81,24 @@ def test_uneven_supercells(shape):
         pic.step(3)
         assert pic.count(0) == n
         assert np.array_equal(pic.get_particles(0)["id"], np.arange(n))
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("shape", ["cic", "tsc", "pcs"])
+def test_species_that_share_a_launch(shape, precision):
+    """Three species without charge states of different density and mass in one
+    launch, and (FP32) one with, in another; an immobile one in neither."""
+    import paper_1606_02862_amd as P
+    cfg = workloads.config(3, nx=24, ny=16, nz=8, shape=shape, precision=precision)
+    el, ion = cfg["species"]
+    plain = dict(el, coincident_with=-1, cap_ppc=None)
+    species = [dict(plain, ppc=5, u_th=0.1), dict(plain, name="light", charge=0.5, mass=3.0, ppc=2, density=0.3, u_th=0.05),
+               dict(plain, name="proton", charge=1.0, mass=1836.0, ppc=7, density=0.9, u_th=0.002)]
+    species.append(dict(plain, name="fixed", charge=1.0, ppc=2, mobile=False) if precision == "fp64" else dict(ion, ionize_into=0))
+    cfg["species"] = species
+    st = oracle.init_state(cfg)
+    g = np.random.default_rng(8)
+    st.E, st.B = (0.05 * g.standard_normal(st.E.shape) for _ in range(2))
+    with P.Pic(cfg) as pic:
+        s0 = parity.shared_start(pic, st)
+        _check(cfg, parity.one_step_errors(pic, cfg, s0))
