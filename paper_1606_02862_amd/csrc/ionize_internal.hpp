@@ -191,6 +191,15 @@ __device__ inline void load_rule(const double* gl, GlRule& rule)
 // One subshell (p, a, b, c, q) with E = p + kT x:
 //   <sigma v>_j = vbar (a q / (p kT)) e^{-p/kT} sum_k w_k ln(1 + x_k r) (1 - b e^{-c x_k r}),  r = kT / p,
 // FP64; the exponential only where b != 0.  The nodes k0, k0 + STEP, ... of the sum.
+//
+// Of the 64 nodes the first GL_SUM are evaluated.  f(x) = ln(1 + x r) is concave
+// with f(0) = 0 and so is 1 - b e^{-c x r} from 1 - b >= 0, so each grows by at
+// most x_k / x_i from node i to a later node k, and the terms from GL_SUM on
+// are at most sum_{k >= GL_SUM} w_k x_k^2 / sum_i w_i x_i^2 = 2^-68 of the sum
+// (2^-72 with b = 0) for every r, b and c: 2^-15 of the sum's last place, below
+// what FP64 holds of it.
+constexpr int GL_SUM = 36;
+static_assert(GL_SUM % 4 == 0, "four lanes share the nodes evenly");
 template <int STEP>
 __device__ inline double lotz_sum(double r, double b, double c, const GlRule& rule, int k0)
 {
@@ -201,11 +210,11 @@ __device__ inline double lotz_sum(double r, double b, double c, const GlRule& ru
             s = fma(rule.w[k] * log1p(xr), b == 0.0 ? 1.0 : 1.0 - b * exp(-c * xr), s);
         }
     } else if (b == 0.0) {
-#pragma unroll 8
-        for (int k = k0; k < GL_NODES; k += STEP) s = fma(rule.w[k], log1p_pos(rule.x[k] * r, rule.lt), s);
+#pragma unroll 9
+        for (int k = k0; k < GL_SUM; k += STEP) s = fma(rule.w[k], log1p_pos(rule.x[k] * r, rule.lt), s);
     } else {
-#pragma unroll 4
-        for (int k = k0; k < GL_NODES; k += STEP) {
+#pragma unroll 3
+        for (int k = k0; k < GL_SUM; k += STEP) {
             const double xr = rule.x[k] * r;
             s = fma(rule.w[k] * log1p_pos(xr, rule.lt), 1.0 - b * exp(-c * xr), s);
         }
@@ -239,11 +248,49 @@ __device__ inline double lotz_shells(double kT, const IonTables& t, int Z, const
 
 __device__ inline double vbar_cm_s(double kT) { return C_CM_S * sqrt(8.0 * kT / (M_PI * ME_C2_EV)); }
 
-template <int LANES = 1>
+// The rate from the shells' sum.
+__device__ inline double rate_of_shells(double kT, double ne, const IonTables& t, int Z, double shells)
+{
+    return ne * vbar_cm_s(kT) / kT * exp(-t.P[Z] / kT) * shells;
+}
+
 __device__ inline double rate_exact(double kT, double ne, const IonTables& t, int Z, const GlRule& rule)
 {
     if (!(kT > 0.0) || !(ne > 0.0)) return 0.0;
-    return ne * vbar_cm_s(kT) / kT * exp(-t.P[Z] / kT) * lotz_shells<LANES>(kT, t, Z, rule);
+    return rate_of_shells(kT, ne, t, Z, lotz_shells(kT, t, Z, rule));
+}
+
+// rate_exact of n pairs by a workgroup: get(i, kT, ne, Z) reads pair i, put(i, nu)
+// takes its rate.  Four lanes share a pair's nodes, a wave 16 pairs; it sums the
+// shells of up to four such groups (its wave's every NW-th) before lane j of each
+// four lanes finishes its pair of group j, so that the prefactor's divisions,
+// root and exponential, about 110 FP64 operations, serve 64 pairs and not 16.
+template <int NT, class Get, class Put>
+__device__ inline void rates_of_pairs(int n, const IonTables& t, const GlRule& rule, Get get, Put put)
+{
+    constexpr int NW = NT / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 3;
+    for (int g0 = 16 * wave; g0 < n; g0 += 4 * 16 * NW) {
+        double mine = 0.0;
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+            const int i = g0 + 16 * NW * q + (lane >> 2);
+            double kT = 0.0, ne = 0.0;
+            int Z = 0;
+            if (i < n) get(i, kT, ne, Z);
+            if (i < n && kT > 0.0 && ne > 0.0) {  // the same in the pair's four lanes
+                const double sum = lotz_shells<4>(kT, t, Z, rule);
+                if (q == j) mine = sum;
+            }
+        }
+        const int i = g0 + 16 * NW * j + (lane >> 2);
+        if (i < n) {
+            double kT, ne;
+            int Z;
+            get(i, kT, ne, Z);
+            put(i, kT > 0.0 && ne > 0.0 ? rate_of_shells(kT, ne, t, Z, mine) : 0.0);
+        }
+    }
 }
 
 __device__ inline double ln_rate_exact(double kT, double ne, const IonTables& t, int Z, const GlRule& rule)

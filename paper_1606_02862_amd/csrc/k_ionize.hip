@@ -69,12 +69,16 @@ __global__ __launch_bounds__(BLOCK) void k_rate_exact(GridView g, PairBuffers pb
     __syncthreads();
     const int n = pb.count[sc];
     const int64_t base = (int64_t)sc * pb.cap;
-    for (int i = tid >> 2; i < n; i += BLOCK / 4) {
-        const int pr = pb.list[base + i];
-        const int64_t gi = cell_index(g, sc, pr & 255);
-        const double v = rate_exact<4>(kT[gi], ne[gi], tab, pr >> 8, rule);
-        if ((tid & 3) == 0) pb.nu[base + i] = v;
-    }
+    rates_of_pairs<BLOCK>(
+        n, tab, rule,
+        [&](int i, double& t, double& d, int& Z) {
+            const int pr = pb.list[base + i];
+            const int64_t gi = cell_index(g, sc, pr & 255);
+            t = kT[gi];
+            d = ne[gi];
+            Z = pr >> 8;
+        },
+        [&](int i, double v) { pb.nu[base + i] = v; });
 }
 
 hipError_t launch_rate_exact(const GridView& g, const PairBuffers& pb, const IonTables& tab, const double* ne,
@@ -232,11 +236,15 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
     }
     const int np = pairs_build(ion, sc, tab.z_max, pl, nullptr,
                                [&](int i, int c, int Z) { s_list[i] = (uint16_t)(c | Z << 8); });
-    for (int i = tid >> 2; i < np; i += BLOCK / 4) {
-        const int pr = s_list[i], c = pr & 255;
-        const double v = rate_exact<4>(mom.acc[1][c], mom.acc[0][c], tab, pr >> 8, rule);
-        if ((tid & 3) == 0) s_nu[i] = v;
-    }
+    rates_of_pairs<BLOCK>(
+        np, tab, rule,
+        [&](int i, double& t, double& d, int& Z) {
+            const int pr = s_list[i], c = pr & 255;
+            t = mom.acc[1][c];
+            d = mom.acc[0][c];
+            Z = pr >> 8;
+        },
+        [&](int i, double v) { s_nu[i] = v; });
     __syncthreads();
     const int n = ion.count[sc];
     const int ebase = el.count[sc];
