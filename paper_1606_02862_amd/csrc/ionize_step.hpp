@@ -141,6 +141,14 @@ __device__ inline int pairs_build(const SpeciesView& ion, int sc, int z_max, Pai
 }
 
 // ---------------------------------------------------------------- events
+// What ion_events takes of a pair's rate: with one event its probability, so
+// that the FP64 exponential is evaluated per pair and not per ion.
+template <bool CHAIN>
+__device__ inline double first_event(double nu, const DrawArgs& a)
+{
+    return CHAIN ? nu : -expm1(-nu * a.dt_phys);
+}
+
 __device__ inline uint64_t word(const Philox4& r, int e)
 {
     return e == 0 ? r.v[0] : e == 1 ? r.v[1] : e == 2 ? r.v[2] : r.v[3];
@@ -151,17 +159,18 @@ __device__ inline uint64_t word(const Philox4& r, int e)
 // event e adding -ln(1 - u_e) / nu_{Z+e} while the running time stays below
 // dt_phys; u_e is word e % 4 of the block of (id, species, 2, step) for e < 4
 // and of (id, species, 6, step) after; later events take the exact rate.
+// first: p (first_event) for one event, nu_Z for several.
 template <bool CHAIN>
-__device__ inline int ion_events(const IonTables& tab, const DrawArgs& a, uint32_t id, int Z0, double nu0, double kT,
+__device__ inline int ion_events(const IonTables& tab, const DrawArgs& a, uint32_t id, int Z0, double first, double kT,
                                  double ne, const GlRule& rule)
 {
     const Philox4 r = philox4x64_10((uint64_t)id, (uint64_t)a.species_index, PURPOSE_IONIZE, (uint64_t)a.step, a.seed, 0);
-    if constexpr (!CHAIN) return u01(r.v[0]) < -expm1(-nu0 * a.dt_phys) ? 1 : 0;
+    if constexpr (!CHAIN) return u01(r.v[0]) < first ? 1 : 0;
     Philox4 r2{};
     double t = 0.0;
     int nev = 0;
     for (int e = 0; e < a.max_events && Z0 + e < tab.z_max; ++e) {
-        const double rate = e == 0 ? nu0 : rate_exact(kT, ne, tab, Z0 + e, rule);
+        const double rate = e == 0 ? first : rate_exact(kT, ne, tab, Z0 + e, rule);
         if (!(rate > 0.0)) break;
         if (e == 4)
             r2 = philox4x64_10((uint64_t)id, (uint64_t)a.species_index, PURPOSE_IONIZE_MORE, (uint64_t)a.step, a.seed, 0);

@@ -127,17 +127,21 @@ __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView i
     __shared__ GlRule rule;
     __shared__ DrawLds s_d;
     __shared__ uint32_t s_info[SC_CELLS];  // the cells' pairs
+    __shared__ double s_first[SC_CELLS * PIC_MAX_ZSTATES];  // first_event of each, sign as in pb.nu
     const int sc = blockIdx.x;
     const int tid = threadIdx.x;
     if (CHAIN) load_rule(db.gl, rule);
     if (tid == 0) s_d = DrawLds{0, 0, 0, 0};
     s_info[tid] = pb.info[(int64_t)sc * SC_CELLS + tid];
+    for (int i = tid, np = pb.count[sc]; i < np; i += BLOCK) {
+        const double nu = pb.nu[(int64_t)sc * pb.cap + i];
+        s_first[i] = copysign(first_event<CHAIN>(fabs(nu), a), nu);
+    }
     __syncthreads();
     const int n = ion.count[sc];
     const int ebase = el.count[sc];
     const int room = el.cap - ebase;
     const int64_t base = (int64_t)sc * ion.cap;
-    const double* const nu = pb.nu + (int64_t)sc * pb.cap;
     bool full = false;
     int fired = 0, active = 0, fb = 0;
     // chunks of DRAW_PER slots per lane: every load of a chunk is issued
@@ -146,7 +150,6 @@ __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView i
     for (int c0 = 0; c0 < n; c0 += BLOCK * DRAW_PER) {
         int zs[DRAW_PER], cells[DRAW_PER];
         uint32_t ids[DRAW_PER];
-        double nus[DRAW_PER];
 #pragma unroll
         for (int k = 0; k < DRAW_PER; ++k) {
             const int t = c0 + k * BLOCK + tid;
@@ -162,24 +165,18 @@ __global__ __launch_bounds__(BLOCK) void k_draw_append(GridView g, SpeciesView i
         }
 #pragma unroll
         for (int k = 0; k < DRAW_PER; ++k) {
-            nus[k] = 0.0;
-            if (zs[k] < tab.z_max) {
-                const uint32_t info = s_info[cells[k]];
-                nus[k] = nu[(info >> PAIR_MASK_BITS) + __popc(info & ((1u << zs[k]) - 1u))];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < DRAW_PER; ++k) {
             const int Z0 = zs[k];
             const int64_t p = base + c0 + k * BLOCK + tid;
             int nev = 0;
             int64_t gi = 0;
             if (Z0 < tab.z_max) {
                 ++active;
-                fb += signbit(nus[k]) ? 1 : 0;  // rated by the exact fallback
+                const uint32_t info = s_info[cells[k]];
+                const double first = s_first[(info >> PAIR_MASK_BITS) + __popc(info & ((1u << Z0) - 1u))];
+                fb += signbit(first) ? 1 : 0;  // rated by the exact fallback
                 // the ion's cell, for later events' rates and the energy account only
                 if (CHAIN || a.energy_loss) gi = cell_index(g, sc, cells[k]);
-                nev = ion_events<CHAIN>(tab, a, ids[k], Z0, fabs(nus[k]), CHAIN ? db.kT[gi] : 0.0,
+                nev = ion_events<CHAIN>(tab, a, ids[k], Z0, fabs(first), CHAIN ? db.kT[gi] : 0.0,
                                         CHAIN ? db.ne[gi] : 0.0, rule);
             }
             const int b = wave_reserve<CHAIN>(nev, &s_d.add);  // every lane of the wave
@@ -210,9 +207,10 @@ hipError_t launch_draw_append(const GridView& g, const SpeciesView& ion, const S
 // supercell (one workgroup each): the electron moments of its cells in LDS
 // (written to the grid as well), the exact rate of each (cell, Z) pair that
 // its ions occupy, four lanes each, and for each ion the draw and append of
-// its events.
+// its events.  Held to four waves per SIMD with one event (one register more
+// and it took 0.35 instead of 0.30 ms on 128^3).
 template <bool CHAIN>
-__global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView ion, SpeciesView el, IonTables tab,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(CHAIN ? 3 : 4))) void k_ionize_exact(GridView g, SpeciesView ion, SpeciesView el, IonTables tab,
                                                         DrawArgs a, DrawBuffers db, double n_ref_over_dv, double* ne,
                                                         double* kT, double* mom4, unsigned long long* counters)
 {
@@ -245,6 +243,10 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
             Z = pr >> 8;
         },
         [&](int i, double v) { s_nu[i] = v; });
+    if constexpr (!CHAIN) {
+        __syncthreads();
+        for (int i = tid; i < np; i += BLOCK) s_nu[i] = first_event<CHAIN>(s_nu[i], a);
+    }
     __syncthreads();
     const int n = ion.count[sc];
     const int ebase = el.count[sc];
@@ -262,9 +264,9 @@ __global__ __launch_bounds__(BLOCK) void k_ionize_exact(GridView g, SpeciesView 
             ++active;
             cell = ion_cell(ion, p);
             const double cne = mom.acc[0][cell], ckT = mom.acc[1][cell];
-            const double nu0 = s_nu[pl.off[cell] + __popc(pl.mask[cell] & ((1u << Z) - 1u))];
+            const double first = s_nu[pl.off[cell] + __popc(pl.mask[cell] & ((1u << Z) - 1u))];
             id = ion.id[p];
-            nev = ion_events<CHAIN>(tab, a, id, Z, nu0, ckT, cne, rule);
+            nev = ion_events<CHAIN>(tab, a, id, Z, first, ckT, cne, rule);
         }
         const int b = wave_reserve<CHAIN>(nev, &s_d.add);
         if (nev) {
