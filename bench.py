@@ -35,7 +35,8 @@ HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
 RATE_COUNTERS = os.path.join(ROOT, "profiles", "rate_exact_fp64_counters.json")
 RATE_SOURCES = [os.path.join(ROOT, "paper_1606_02862_amd", "csrc", f)
-                for f in ("k_ionize.hip", "ionize_internal.hpp", "pic_device.hpp", "pic_internal.hpp")]
+                for f in ("k_ionize.hip", "ionize_step.hpp", "ionize_internal.hpp", "rate_log.hpp", "pic_device.hpp",
+                          "pic_internal.hpp")]
 PROFILE_COUNTERS = os.path.join(ROOT, "profiles", "push_shear128_counters.json")
 PUSH_SOURCES = [os.path.join(ROOT, "paper_1606_02862_amd", "csrc", f)
                 for f in ("k_push.hip", "pic_deposit.hpp", "pic_migrate.hpp", "pic_device.hpp", "pic_internal.hpp")]
@@ -202,7 +203,7 @@ def counter_summary(fetch_dir: str, write_dir: str, copy_fetch_dir: str, copy_wr
     benchmark, then of --copy-calibration) into the counter summary that
     roofline.traffic is computed from, stamped with the particle kernel's
     source hash."""
-    push = "k_push<1, false, false, 256, float>"
+    push = "k_push<1, false, false, 256, float"
 
     def push_avg(run_dir, counter):
         v = [float(r["Counter_Value"]) for r in _counter_rows(run_dir)
