@@ -132,13 +132,6 @@ __device__ inline R interp_n(const R* f0, const R* wx, const R* wy, const R* wz)
     }
     return acc;
 }
-template <int ORDER, class R>
-__device__ inline R interp(const R* f0, const R* wx, const R* wy, const R* wz)
-{
-    constexpr int P = ORDER + 1;
-    return interp_n<ORDER, P, P, P>(f0, wx, wy, wz);
-}
-
 // Fixed-point contribution (v already scaled, |v| <= 2^30), truncated to
 // int32 and added as a sign-extended int64.  Truncation moves each
 // contribution by less than 2^-30 vmax.
@@ -168,22 +161,15 @@ __device__ inline const E& at(const E* base, unsigned byte_off)
     return *reinterpret_cast<const E*>(reinterpret_cast<const char*>(base) + byte_off);
 }
 
-// Particle streams of the frame loop (read once, written once per step):
-// with STREAM the loads and stores carry the non-temporal hint.  Measured
-// about 1 % faster for CIC and slightly slower for TSC, so only CIC sets it.
+// Weights of the frame loop (read once per step): with STREAM the load carries
+// the non-temporal hint, like the triples below.  Measured about 1 % faster for
+// CIC and slightly slower for TSC, so only CIC sets it.
 template <bool STREAM, typename E>
 __device__ inline E ld_part(const E* base, unsigned byte_off)
 {
     if constexpr (STREAM) return __builtin_nontemporal_load(&at(base, byte_off));
     else return at(base, byte_off);
 }
-template <bool STREAM, typename E>
-__device__ inline void st_part(E* base, unsigned byte_off, E v)
-{
-    if constexpr (STREAM) __builtin_nontemporal_store(v, &at(base, byte_off));
-    else at(base, byte_off) = v;
-}
-
 // Triples (FP32) of the frame loop with the non-temporal hint: the hint keeps
 // the compiler from merging three scalar accesses, so the 12-byte buffer
 // instructions are named.  `rs` spans the slab's triples.
