@@ -102,3 +102,27 @@ def test_species_that_share_a_launch(shape, precision):
     with P.Pic(cfg) as pic:
         s0 = parity.shared_start(pic, st)
         _check(cfg, parity.one_step_errors(pic, cfg, s0))
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("box", [(16, 16, 8), (72, 64, 32)])
+def test_large_ids_survive_migration(box, precision):
+    """Ids whose bits read as NaN, infinity and negative floats travel through the
+    arrival records (as the fourth real of one) unchanged."""
+    import paper_1606_02862_amd as P
+    cfg = workloads.config(1, nx=box[0], ny=box[1], nz=box[2], shape="cic", precision=precision)
+    cfg["species"][0].update(ppc=2, u_th=0.5)
+    with P.Pic(cfg) as pic:
+        p = pic.get_particles(0)
+        n = len(p["id"])
+        base = np.array([0x7F800000, 0x7FC00000, 0xFF800000, 0xFFFFFFFF - n], dtype=np.int64)
+        p["id"] = base[np.arange(n) % 4] + np.arange(n) // 4
+        pic.set_particles(0, p)
+        for k in (1, 3, 4):
+            pic.step(k)
+        q = pic.get_particles(0)
+    order = np.argsort(p["id"])
+    assert np.array_equal(q["id"], p["id"][order])
+    assert np.array_equal(q["w"], p["w"][order])
+    moved = np.floor(q["x"] / 8) != np.floor(p["x"][order] / 8)
+    assert moved.sum() > n // 10
