@@ -24,6 +24,8 @@
 // 64^3 with 7 particles per cell 81 / 73, 96x64x64 107 / 99, 128x96x64
 // 169 / 165, 128^3 with 16 equal, 256x256x128 1 % slower (the fused form moves J
 // once more); FP64 64^3 118 / 110, 96x64x64 145 / 144, 128x64x64 199 / 205.
+#include <type_traits>
+
 #include "pic_migrate.hpp"
 
 namespace pic {
@@ -197,6 +199,25 @@ __global__ __launch_bounds__(BLOCK) void k_yee_head(GridViewT<R> g, FieldScratch
         st4(f.Jacc + c, zero);
         st4(f.Jacc + N + c, zero);
         st4(f.Jacc + 2 * N + c, zero);
+    }
+    if constexpr (std::is_same<R, float>::value) {
+        for (int s = 0; s < f.n_fix; ++s) {  // species deposited in several parts
+            ulonglong2* const a = reinterpret_cast<ulonglong2*>(f.fix[s]);
+            Quad<R>* const j[3] = {&jx, &jy, &jz};
+            ulonglong2 v[3][2];
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) v[d][h] = a[(d * N + c) / 2 + h];
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    j[d]->v[2 * h] += (R)((double)(long long)v[d][h].x * f.inv[s]);
+                    j[d]->v[2 * h + 1] += (R)((double)(long long)v[d][h].y * f.inv[s]);
+                    a[(d * N + c) / 2 + h] = make_ulonglong2(0ull, 0ull);
+                }
+        }
     }
     if (keep_j) {
         st4(g.J + c, jx);

@@ -194,11 +194,15 @@ __device__ inline void st3_stream(__amdgpu_buffer_rsrc_t rs, unsigned byte_off, 
 // Add one node of a supercell's fixed-point current tile to global J: as an
 // FP32 atomic, or (PIC_OPT_DETERMINISTIC_J) rescaled to the cycle's common
 // scale (jratio <= 1, rounded to nearest) and added to the 64-bit fixed-point
-// J, whose integer sums do not depend on the order of the tiles.
-__device__ inline void flush_node(const GridView& g, int i, long long iv, float jinv, double jratio)
+// J, whose integer sums do not depend on the order of the tiles.  With jfix
+// (PushItemT) the tile is one of several of its supercell and added as it is.
+__device__ inline void flush_node(const GridView& g, int i, long long iv, float jinv, double jratio,
+                                  unsigned long long* jfix)
 {
     if (iv == 0) return;
-    if (g.J64) {
+    if (jfix) {
+        atomicAdd(&jfix[i], (unsigned long long)iv);
+    } else if (g.J64) {
         const long long v = jratio == 1.0 ? iv : __double2ll_rn((double)iv * jratio);
         if (v != 0) atomicAdd(&g.J64[i], (unsigned long long)v);
     } else {
@@ -211,7 +215,7 @@ __device__ inline void flush_node(const GridView& g, int i, long long iv, float 
 // leave most of the chip idle (split_parts): `parts` workgroups of SPLIT_NT lanes per
 // supercell, part p taking every parts-th frame from frame p.  Each stages the
 // fields and flushes a current tile of its own (the flush adds atomically
-// already); the supercell's hole list is shared, each part reserving its
+// already, in FP32 to integer sums); the supercell's hole list is shared, each part reserving its
 // range after its frame loop from a list of its own; the frames are
 // dense when the kernel starts, since the field update's last kernel absorbs
 // the arrivals of every cycle.  One launch takes every species with the same
@@ -234,6 +238,7 @@ void k_push(GridViewT<R> g, PushArgsT<R> args, int apar, int wpar)
     const SpeciesViewT<R>& s = ps.s;
     const R jscale = ps.jscale, jinv = ps.jinv;
     const double jratio = ps.jratio;
+    unsigned long long* const jfix = SPLIT ? ps.jfix : nullptr;
     const int parts = ps.parts, blk = (int)blockIdx.x - (SPLIT ? ps.first : 0);
     using T = Tile<ORDER, R>;
     using A = JAcc<R>;
@@ -748,7 +753,7 @@ void k_push(GridViewT<R> g, PushArgsT<R> args, int apar, int wpar)
                 if (tz >= PcsTile::jz(c)) continue;
                 if constexpr (std::is_same<R, float>::value) {
                     const long long iv = (long long)tJ[PcsTile::joff(c) + t];
-                    flush_node(g, c * N + gi, iv, jinv, jratio);
+                    flush_node(g, c * N + gi, iv, jinv, jratio, jfix);
                 } else {
                     const double v = tJ[PcsTile::joff(c) + t];
                     if (v != 0.0) unsafeAtomicAdd(&g.J[c * N + gi], v);
@@ -767,7 +772,7 @@ void k_push(GridViewT<R> g, PushArgsT<R> args, int apar, int wpar)
             for (int c = 0; c < 3; ++c) {
                 if constexpr (std::is_same<R, float>::value) {
                     const long long iv = (long long)tJ[c * T::JN + t];
-                    flush_node(g, c * N + gi, iv, jinv, jratio);
+                    flush_node(g, c * N + gi, iv, jinv, jratio, jfix);
                 } else {
                     const double v = tJ[c * T::JN + t];
                     if (v != 0.0) unsafeAtomicAdd(&g.J[c * N + gi], v);
@@ -836,6 +841,8 @@ hipError_t launch_push(const GridViewT<R>& g, const PushItemT<R>* items, int n, 
         // a tile rescaled to the common scale is rounded once per node: order-independent only as one tile per supercell
         if (parts > 1 && p.jratio != 1.0) parts = 1;
         p.parts = split ? parts : 1;
+        p.jfix = std::is_same<R, float>::value && !g.J64 && p.parts > 1 ? items[k].jfix : nullptr;
+        if (std::is_same<R, float>::value && !g.J64 && p.parts > 1 && !p.jfix) return hipErrorInvalidValue;
         p.first = blocks;
         blocks += g.nsc * p.parts;
     }

@@ -305,6 +305,10 @@ int alloc_species(pic_ctx* c, int s)
         if (!(v.zs = (uint8_t*)dev_alloc(c, n))) return fail(c, PIC_ERR_OOM, "species %d: charge states", s);
         if (!(v.izs = (uint8_t*)dev_alloc(c, ni))) return fail(c, PIC_ERR_OOM, "species %d: arrivals", s);
     }
+    S.jfix = nullptr;
+    if (!c->fp64 && !c->g.J64 && d.mobile && v.parts > 1 &&
+        !(S.jfix = (unsigned long long*)dev_alloc(c, (size_t)3 * c->grid.nx * c->grid.ny * c->grid.nz * 8)))
+        return fail(c, PIC_ERR_OOM, "species %d: fixed-point current", s);
     if (!(v.holes = (int32_t*)dev_alloc(c, ni * 4))) return fail(c, PIC_ERR_OOM, "species %d: holes", s);
     v.left = nullptr;
     if (v.parts && !(v.left = (int32_t*)dev_alloc(c, (size_t)nsc * v.parts * cap_in * 4)))
@@ -780,7 +784,7 @@ template <class R>
 int step_t(pic_ctx* c, int n)
 {
     GridViewT<R>& g = gview<R>(c);
-    const FieldScratchT<R>& fs = fscratch<R>(c);
+    FieldScratchT<R> fs = fscratch<R>(c);
     const int64_t N = (int64_t)c->grid.nx * c->grid.ny * c->grid.nz;
     const double dt = c->grid.dt;
     for (int it = 0; it < n; ++it) {
@@ -806,6 +810,23 @@ int step_t(pic_ctx* c, int n)
         if (!c->jacc_clear) {
             if (g.J64) HIPCHK(c, launch_zero_f64(reinterpret_cast<double*>(g.J64), 3 * N, c->stream));  // all-zero bits
             else HIPCHK(c, launch_zero_r(gp.J, 3 * N, c->stream));
+            for (int s = 0; s < c->nsp; ++s)
+                if (c->sp[s].jfix) HIPCHK(c, launch_zero_f64(reinterpret_cast<double*>(c->sp[s].jfix), 3 * N, c->stream));
+        }
+        // species deposited in several parts: one accumulator for those of one scale
+        unsigned long long* jfix[PIC_MAX_SPECIES] = {};
+        fs.n_fix = 0;
+        for (int s = 0; s < c->nsp; ++s) {
+            if (!c->sp[s].jfix) continue;
+            const double inv = 1.0f / fixed_scale(push_vmax(c, s));  // as launch_push scales the tiles
+            int k = 0;
+            while (k < fs.n_fix && fs.inv[k] != inv) ++k;
+            if (k == fs.n_fix) {
+                fs.fix[k] = c->sp[s].jfix;
+                fs.inv[k] = inv;
+                ++fs.n_fix;
+            }
+            jfix[s] = fs.fix[k];
         }
         c->jacc_clear = false;
         // step `it` writes its leavers to parity it & 1 and absorbs the previous step's
@@ -826,7 +847,7 @@ int step_t(pic_ctx* c, int n)
             };
             for (int s = 0; s < c->nsp; ++s) {
                 if (!c->sp[s].desc.mobile || (c->sp[s].desc.z_max > 0) != (z == 1)) continue;
-                items[n_items++] = PushItemT<R>{&sview<R>(c, s), push_vmax(c, s), c->sp[s].v.parts};
+                items[n_items++] = PushItemT<R>{&sview<R>(c, s), push_vmax(c, s), c->sp[s].v.parts, jfix[s]};
                 if (!c->split) HIPCHK(c, flush());
             }
             HIPCHK(c, flush());
@@ -966,8 +987,8 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
     c->fused = N * (c->fp64 ? 8 : 4) <= FUSE_BYTES;
     for (void*& p : fsp)
         if (c->fused) fields_ok = fields_ok && (p = dev_alloc(c, fbytes));
-    c->fs = FieldScratchT<float>{(float*)fsp[0], (float*)fsp[1], (float*)fsp[2]};
-    c->fs64 = FieldScratchT<double>{(double*)fsp[0], (double*)fsp[1], (double*)fsp[2]};
+    c->fs.E = (float*)fsp[0]; c->fs.B = (float*)fsp[1]; c->fs.Jacc = (float*)fsp[2];
+    c->fs64.E = (double*)fsp[0]; c->fs64.B = (double*)fsp[1]; c->fs64.Jacc = (double*)fsp[2];
     if (!fields_ok) {
         c->err = "device allocation of fields failed";
         return bail(PIC_ERR_OOM);

@@ -96,6 +96,7 @@ struct Species {
     double weight;
     double wmax;           // bound of |w| that sets the fixed-point current scale (>= wheld)
     double wheld;          // largest |w| known to be held (init, set, ionisation electrons)
+    unsigned long long* jfix;  // 3 * N fixed-point current, FP32 species of several parts (PushItemT), or nullptr
 };
 
 // Map a workgroup index to a supercell so that the 8 XCDs (which receive
@@ -134,11 +135,18 @@ inline hipError_t launch_zero_r(double* p, int64_t n, hipStream_t st) { return l
 // galerkin: the reduced-order gather along staggered axes (PIC_GATHER_GALERKIN)
 // jscale_g: with g.J64, the cycle's common fixed-point scale (2^30 over the
 // largest vmax of the cycle's species); each tile is rescaled to it at the flush
+// jfix: FP32 without g.J64, parts > 1: 3 * N fixed-point sums at the species' own
+// scale (shared by species of one scale) that its tiles are added to instead of
+// g.J.  A supercell's current is then one exact integer sum whatever the number
+// of its parts; FP32 additions of partial tiles would round each of them.  The
+// 64-bit atomics cost 2 to 5 % of a cycle (four cycles of two TSC species on 64
+// supercells 230 us, 217 with FP32 ones, 590 with one workgroup per supercell).
 template <class R>
 struct PushItemT {
     const SpeciesViewT<R>* s;
     double vmax;
     int parts;
+    unsigned long long* jfix;
 };
 template <class R>
 hipError_t launch_push(const GridViewT<R>& g, const PushItemT<R>* items, int n, int order, bool galerkin,
@@ -149,6 +157,7 @@ struct PushSpeciesT {
     SpeciesViewT<R> s;
     R jscale, jinv;
     double jratio;
+    unsigned long long* jfix;
     int parts, first;
 };
 template <class R>
@@ -203,11 +212,15 @@ hipError_t launch_yee_e(const GridViewT<R>& g, double coef, hipStream_t st);
 // The fused field update (k_fields.hip), for grids whose field components take up to FUSE_BYTES each.
 // Scratch of 3 * N values each: the fields between its two kernels, and the
 // current accumulators the deposit adds to, zero between cycles (unused with
-// g.J64, whose sums are cleared the same way).
+// g.J64, whose sums are cleared the same way): Jacc, and n_fix arrays of
+// fixed-point sums (PushItemT), each of which times its inv is rounded to FP32 once.
 constexpr int64_t FUSE_BYTES = 3 << 20;
 template <class R>
 struct FieldScratchT {
     R *E, *B, *Jacc;
+    unsigned long long* fix[PIC_MAX_SPECIES];
+    double inv[PIC_MAX_SPECIES];
+    int n_fix;
 };
 // Species whose arrivals of parity par the tail's first workgroups absorb.
 template <class R>
