@@ -124,6 +124,7 @@ void* dev_alloc(pic_ctx* c, size_t bytes)
         p = nullptr;
     }
     if (p) c->owned.push_back(p);
+    else (void)hipGetLastError();  // a refused hipMalloc: the launches that follow return hipGetLastError()
     return p;
 }
 
