@@ -171,7 +171,11 @@ typedef struct {
 
 /* Device-memory provider.  alloc returns device memory of at least `bytes`
  * bytes aligned to 256 B (NULL on failure; a pointer that is not so aligned
- * is handed back to free and counts as a failure); free releases it. */
+ * is handed back to free and counts as a failure); free releases it.  Besides
+ * pic_init, pic_get_particles(64), pic_rate_eval, pic_mlp_train and
+ * pic_mlp_loss_grad take and give back scratch.  The memory is used by kernels
+ * on the handle's stream only: an allocator that reuses blocks in the order of a
+ * stream has to do so in the order of the handle's. */
 typedef struct {
     void* (*alloc)(size_t bytes, void* user);
     void (*free)(void* ptr, void* user);

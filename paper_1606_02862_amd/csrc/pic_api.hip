@@ -550,13 +550,19 @@ bool export_particles(pic_ctx* c, int s, V* v, int& rc)
     const SpeciesViewT<R>& sv = sview<R>(c, s);
     const int nsc = c->g.nsc;
     if ((int64_t)nsc * sv.cap > 0xFFFFFFFFLL) return false;
-    struct Scratch {  // given back on every path
+    struct Scratch {  // given back on every path, when no kernel uses it any more
         pic_ctx* c;
         void* p[4] = {};
-        ~Scratch() { for (void* q : p) dev_free(c, q); }
+        bool idle = true;
+        ~Scratch()
+        {
+            if (!idle) (void)hipStreamSynchronize(c->stream);
+            for (void* q : p) dev_free(c, q);
+        }
     } m{c};
     auto run = [&](hipError_t e, const char* what) {
         if (e == hipSuccess) return true;
+        m.idle = false;
         rc = fail(c, PIC_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
         return false;
     };

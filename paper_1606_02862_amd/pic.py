@@ -105,6 +105,24 @@ class TorchAllocator:
         self.live.pop(ptr, None)
 
 
+class _OnStream:
+    """An allocator's callbacks for one handle, called with the handle's stream
+    current: PyTorch's caching allocator orders the reuse of a block on the
+    stream that is current when it hands it out, and the library's kernels run
+    on the handle's, whatever stream the caller works on by then."""
+
+    def __init__(self, allocator, stream):
+        import torch
+        self.inner = allocator  # owns the callbacks of its struct
+
+        def alloc(nbytes, user):
+            with torch.cuda.stream(stream):
+                return allocator.struct.alloc(nbytes, user)
+
+        self._alloc = A.ALLOC_FN(alloc)
+        self.struct = A.AllocT(self._alloc, allocator.struct.free, allocator.struct.user)
+
+
 class Pic:
     """One simulation on one GPU.  cfg is a workload dictionary (see
     workloads.py).  stream: a torch.cuda.Stream (default: the current one)."""
@@ -121,7 +139,9 @@ class Pic:
         self.fp64 = cfg["grid"].get("precision", "fp32") == "fp64"
         self._rt = np.float64 if self.fp64 else np.float32  # host type of momenta, weights and fields
         # allocator: an object with .struct (an AllocT), e.g. a TorchAllocator
-        self._alloc = allocator if allocator is not None else (TorchAllocator(self.device) if torch_alloc else None)
+        if allocator is None and torch_alloc:
+            allocator = TorchAllocator(self.device)
+        self._alloc = _OnStream(allocator, self.stream) if allocator is not None else None
         self._g = grid_struct(cfg)
         self._s = species_structs(cfg)
         h = C.c_void_p()
