@@ -4,18 +4,17 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <limits>
 #include <string>
-#include <thread>
 #include <type_traits>
 #include <vector>
 
 #include "ionize_internal.hpp"
+#include "page_touch.hpp"
 
 using namespace pic;
 
@@ -510,35 +509,6 @@ int64_t host_count(pic_ctx* c, int s, std::vector<int32_t>& counts)
     for (int32_t v : counts) t += v;
     return t;
 }
-
-// Touches every page of the caller's output arrays from a few threads.  Fresh
-// arrays have no pages yet, and the copies that follow would fault them in one
-// by one on a single core (half of a 7 ms checkpoint of 0.9 M particles).
-struct PageToucher {
-    std::vector<std::thread> threads;
-    void start(const std::array<std::pair<char*, size_t>, 9>& spans)
-    {
-        size_t bytes = 0;
-        for (const auto& a : spans) bytes += a.second;
-        const unsigned cores = std::thread::hardware_concurrency();
-        const size_t n = std::min<size_t>({bytes >> 22, 8, cores ? cores : 1});  // a thread per 4 MiB
-        try {
-            for (size_t t = 0; t < n; ++t)
-                threads.emplace_back([=] {
-                    for (const auto& a : spans)
-                        for (size_t b = a.second / n * t, e = t + 1 == n ? a.second : a.second / n * (t + 1); b < e; b += 4096)
-                            *(volatile char*)(a.first + b) = 0;
-                });
-        } catch (...) {  // no thread or memory to spare: the copies fault the rest in
-        }
-    }
-    void join()
-    {
-        for (std::thread& t : threads) t.join();
-        threads.clear();
-    }
-    ~PageToucher() { join(); }
-};
 
 // The species' particles in id order by way of k_export.hip.  Returns false,
 // with rc untouched, where the host has to sort (duplicate or very sparse ids,
