@@ -4,6 +4,7 @@ a stream-ordered allocator then hands out blocks that nothing queued on another
 stream still uses."""
 import contextlib
 import ctypes as C
+import types
 
 import numpy as np
 import pytest
@@ -33,7 +34,8 @@ class _Recording:
 
 def test_callbacks_run_with_the_handles_stream_current(monkeypatch):
     from paper_1606_02862_amd import pic as M
-    current = ["caller"]
+    caller, one, two = (types.SimpleNamespace(device="cuda:0", name=n) for n in ("caller", "one", "two"))
+    current = [caller]
 
     @contextlib.contextmanager
     def stream(s):
@@ -42,11 +44,14 @@ def test_callbacks_run_with_the_handles_stream_current(monkeypatch):
         current[0] = before
 
     monkeypatch.setattr(torch.cuda, "stream", stream)
-    inner = _Recording(lambda: current[0], lambda n: 4096 if n == 256 else None)
-    a, b = M._OnStream(inner, "one"), M._OnStream(inner, "two")  # one allocator, two handles
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: current[0])
+    inner = _Recording(lambda: current[0].name, lambda n: 4096 if n == 256 else None)
+    a, b = M._OnStream(inner, one), M._OnStream(inner, two)  # one allocator, two handles
     assert a.struct.alloc(256, None) == 4096 and b.struct.alloc(256, None) == 4096
     assert a.struct.alloc(512, None) is None
-    assert inner.seen == ["one", "two", "one"] and current == ["caller"]
+    assert inner.seen == ["one", "two", "one"] and current == [caller]
+    current[0] = two
+    assert b.struct.alloc(256, None) == 4096 and inner.seen[-1] == "two" and current == [two]
     a.struct.free(C.c_void_p(4096), None)
     assert inner.freed == [4096]
 
