@@ -41,8 +41,9 @@ constexpr int CNT_ACTIVE = 8, CNT_FIRED = CNT_ACTIVE + CNT_STRIPES, CNT_FBIONS =
 // info = off << PAIR_MASK_BITS | mask.
 constexpr int PAIR_MASK_BITS = 16;
 static_assert(PIC_MAX_ZSTATES <= PAIR_MASK_BITS, "one mask bit per charge state");
+inline int pair_cap(int z_max, int ion_slots) { return SC_CELLS * z_max < ion_slots ? SC_CELLS * z_max : ion_slots; }
 struct PairBuffers {
-    int cap;             // pairs per supercell: 256 z_max
+    int cap;             // pairs per supercell: 256 z_max, at most one for each ion slot (pair_cap)
     uint16_t* list;      // [nsc][cap]
     uint32_t* info;      // [nsc][256]
     int32_t* count;      // [nsc]

@@ -50,7 +50,7 @@ hipError_t launch_moments_pairs(const GridView& g, const SpeciesView& e, const S
                                 const PairBuffers& pb, double n_ref_over_dv, double* ne, double* kT, double* mom4,
                                 hipStream_t st)
 {
-    if (pb.cap < SC_CELLS * z_max) return hipErrorInvalidValue;
+    if (pb.cap < pair_cap(z_max, ion.cap)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_moments_pairs, dim3(g.nsc), dim3(BLOCK), 0, st, g, e, ion, z_max, pb, n_ref_over_dv, ne, kT,
                        mom4);
     return hipGetLastError();

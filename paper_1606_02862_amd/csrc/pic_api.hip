@@ -349,7 +349,7 @@ int alloc_ionisation(pic_ctx* c)
     for (int s = 0; s < c->nsp; ++s) {
         if (c->sp[s].desc.z_max == 0) continue;
         PairBuffers& pb = c->pairs[s];
-        pb.cap = SC_CELLS * c->sp[s].desc.z_max;
+        pb.cap = pair_cap(c->sp[s].desc.z_max, c->sp[s].v.cap);
         const size_t npair = (size_t)c->g.nsc * pb.cap;
         if (!(pb.nu = (double*)dev_alloc(c, npair * 8)) || !(pb.list = (uint16_t*)dev_alloc(c, npair * 2)) ||
             !(pb.info = (uint32_t*)dev_alloc(c, (size_t)N * 4)) ||
