@@ -557,9 +557,10 @@ def main(argv=None):
     # cycle, so they stay out of the region `value` is timed on
     tm = timed_kernels(P, torch, cfg, args.warmup, args.steps)
 
-    push_avg_ms = tm["push_ms"] / max(tm["push_launches"], 1)
-    per_launch = algorithmic_bytes_per_push(n_particles // max(1, sum(1 for s in cfg["species"] if s["mobile"])),
-                                            ncell, order, es)
+    launches = max(tm["push_launches"], 1)  # on small grids species share one
+    push_avg_ms = tm["push_ms"] / launches
+    mobile = max(1, sum(1 for s in cfg["species"] if s["mobile"]))
+    per_launch = algorithmic_bytes_per_push(n_particles // mobile, ncell, order, es) * mobile * args.steps // launches
     achieved = per_launch / (push_avg_ms * 1e-3) / 1e9
     # the counter summary covers the default FP32 workload only
     traffic = None if (args.fp64 or overridden or args.config != 1) else traffic_from_profile(n_particles)

@@ -305,7 +305,7 @@ typedef struct {
     double push_ms;        /* particle kernel (gather+push+deposit), all species */
     double migrate_ms;     /* supercell migration */
     double field_ms;       /* J zero + Yee updates */
-    int64_t push_launches;
+    int64_t push_launches; /* launches of the particle kernel; on small grids species share one */
     int64_t push_particles; /* particles processed by the timed push launches */
 } pic_timing_t;
 int pic_timing(pic_ctx* ctx, int enable, pic_timing_t* out);

@@ -823,7 +823,7 @@ int step_t(pic_ctx* c, int n)
                                                               c->grid.gather == PIC_GATHER_GALERKIN, jscale_g, apar,
                                                               wpar, c->stream)
                                              : hipSuccess;
-                c->pending_launches += c->timing ? n_items : 0;
+                c->pending_launches += c->timing && n_items ? 1 : 0;
                 n_items = 0;
                 return e;
             };
