@@ -115,7 +115,8 @@ class _OnStream:
         import torch
         self.inner = allocator  # owns the callbacks of its struct
 
-        give = allocator.struct.alloc
+        # past its C callback where it is this module's own (1.5 us a request)
+        give = allocator._do_alloc if isinstance(allocator, TorchAllocator) else allocator.struct.alloc
 
         def alloc(nbytes, user):
             if torch.cuda.current_stream(stream.device) == stream:  # the context costs 10 us
