@@ -114,12 +114,14 @@ class _OnStream:
     def __init__(self, allocator, stream):
         import torch
         self.inner = allocator  # owns the callbacks of its struct
+        self.current = False    # set while the stream is known to be current
 
         # past its C callback where it is this module's own (1.5 us a request)
         give = allocator._do_alloc if isinstance(allocator, TorchAllocator) else allocator.struct.alloc
 
         def alloc(nbytes, user):
-            if torch.cuda.current_stream(stream.device) == stream:  # the context costs 10 us
+            # the context costs 10 us, the look 2
+            if self.current or torch.cuda.current_stream(stream.device) == stream:
                 return give(nbytes, user)
             with torch.cuda.stream(stream):
                 return give(nbytes, user)
@@ -150,9 +152,14 @@ class Pic:
         self._g = grid_struct(cfg)
         self._s = species_structs(cfg)
         h = C.c_void_p()
-        rc = self.lib.pic_init(C.byref(h), C.byref(self._g), self._s, self.nsp, _SHAPE[cfg["grid"]["shape"]],
-                               C.byref(self._alloc.struct) if self._alloc else None,
-                               C.c_void_p(self.stream.cuda_stream))
+        with torch.cuda.stream(self.stream):  # once for the many requests of pic_init
+            if self._alloc:
+                self._alloc.current = True
+            rc = self.lib.pic_init(C.byref(h), C.byref(self._g), self._s, self.nsp, _SHAPE[cfg["grid"]["shape"]],
+                                   C.byref(self._alloc.struct) if self._alloc else None,
+                                   C.c_void_p(self.stream.cuda_stream))
+            if self._alloc:
+                self._alloc.current = False
         A.check(rc, None)
         self.h = h
 
