@@ -200,8 +200,14 @@ int pic_init(pic_ctx** out, const pic_grid_t* grid, const pic_species_t* species
  * particles that left it to their destination's arrival list; then B half
  * step, E full step with -J, B half step.  After the last cycle one migration
  * pass takes in the last arrivals, so the frames are dense when the call
- * returns.  Asynchronous on the stream except for one small read of the
- * device error flags at the end (PIC_ERR_CAPACITY, PIC_ERR_CFL). */
+ * returns.  Small grids run the same cycle in fewer launches: up to 3 MiB per
+ * field component the field update takes two, clears the current for the next
+ * cycle and takes in a call's last arrivals; up to 512 supercells species share
+ * a particle-kernel launch, several workgroups share a supercell (its FP32
+ * current still one exact fixed-point sum, rounded once), and every cycle's
+ * arrivals are taken in by the field update.  Asynchronous on the stream except
+ * for one wait at the end, after which the error flags are read from pinned
+ * host memory (PIC_ERR_CAPACITY, PIC_ERR_CFL). */
 int pic_step(pic_ctx* ctx, int n);
 
 typedef struct {
@@ -259,7 +265,8 @@ int pic_set_run_state(pic_ctx* ctx, const pic_run_state_t* in);
 /* Particle transfer.  Host arrays of `count` entries; positions are global,
  * in cell units, inside [0, n_d).  zstate may be NULL for species without
  * charge states.  get returns particles sorted by id; capacity is the length
- * of the caller's arrays (PIC_ERR_ARG if too small).  set replaces the
+ * of the caller's arrays (PIC_ERR_ARG if too small), which keep their contents
+ * until the particles are copied in.  set replaces the
  * species' particles (PIC_ERR_CAPACITY if a supercell's frames overflow). */
 typedef struct {
     int64_t count;
@@ -302,9 +309,9 @@ int pic_mark_reference(pic_ctx* ctx);
 /* Per-kernel GPU time accounting (HIP events around each launch of pic_step
  * on the handle's stream).  enable = 1 starts accumulating, 0 stops. */
 typedef struct {
-    double push_ms;        /* particle kernel (gather+push+deposit), all species */
+    double push_ms;        /* particle kernel (gather+push+deposit), all species, with the zeroing of J if it has a launch */
     double migrate_ms;     /* supercell migration */
-    double field_ms;       /* J zero + Yee updates */
+    double field_ms;       /* Yee updates (on small grids they zero J) */
     int64_t push_launches; /* launches of the particle kernel; on small grids species share one */
     int64_t push_particles; /* particles processed by the timed push launches */
 } pic_timing_t;
@@ -323,7 +330,8 @@ int pic_timing(pic_ctx* ctx, int enable, pic_timing_t* out);
  *     of their cross-sections (pic_lotz_shell_t) averaged over a Maxwellian,
  *     evaluated per subshell (p, a, b, c, q) as
  *       vbar (a q / (p kT)) e^{-p/kT} sum_k w_k ln(1 + x_k r) (1 - b e^{-c x_k r}),  r = kT / p
- *     with the 64-point Gauss-Laguerre rule (x_k, w_k) in FP64 (PIC_RATE_EXACT),
+ *     with the 64-point Gauss-Laguerre rule (x_k, w_k) in FP64 (PIC_RATE_EXACT;
+ *     nodes whose terms lie below FP64's last place of the sum are left out),
  *     by the learned surrogate (PIC_RATE_MLP, see below), or from a table
  *     (PIC_RATE_TABLE): per state Z, h_Z = ln of the subshell sum
  *     sum_j (a_j q_j / p_j) e^{-(p_j - P)/kT} S_j at 1024 points uniform in
@@ -373,8 +381,8 @@ typedef struct {
 int pic_ionize(pic_ctx* ctx, pic_rate_mode_t mode, pic_ionize_stats_t* out);
 
 /* The same step as three launches over the whole grid: cell moments, the
- * rate of every ion, then the draw and append, with the rate stage timed on
- * its own (rate_ms). */
+ * rate of every (cell, Z) pair that holds ions, then the draw and append, with
+ * the rate stage timed on its own (rate_ms). */
 int pic_ionize_staged(pic_ctx* ctx, pic_rate_mode_t mode, pic_ionize_stats_t* out);
 
 /* Per-cell n_e (cm^-3) and kT_e (eV) of the electrons that species `species`

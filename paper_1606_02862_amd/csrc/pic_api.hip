@@ -1252,9 +1252,9 @@ int pic_set_fields64(pic_ctx* c, const double* E, const double* B, const double*
 
 namespace {
 
-// One ionisation step.  Staged: the cell moments, the rate of every ion and
-// the draw and append as three launches over the grid (the rate stage timed
-// on its own).  Fused (the exact rate): one launch that does all three per
+// One ionisation step.  Staged: the cell moments with the (cell, Z) pairs that
+// hold ions, the rate of every pair and the draw and append as three launches
+// over the grid (the rate stage timed on its own).  Fused (the exact rate): one launch that does all three per
 // supercell, so that the moments' streams of some workgroups overlap the
 // FP64 quadrature of others.  The surrogate and the table always run staged:
 // fused into the surrogate's persistent kernel (three waves per SIMD for its

@@ -1,15 +1,17 @@
 // ln(1 + y) in FP64 for the rate quadrature, y >= 0.
 //
-// The quadrature is bound by its logarithms (64 per rate), and the library
+// The quadrature is bound by its logarithms (36 per rate, GL_SUM), and the library
 // log1p serves every argument at about 120 FP64 operations.  Here y >= 0 and
-// the 64 terms share one table in LDS, so about 18 do: u = fl(1 + y) = 2^e m
+// the terms share one table in LDS, so about 18 do, by the table-driven method
+// of Tang (1990, ACM TOMS 16, 378): u = fl(1 + y) = 2^e m
 // with m in [1, 2), the table interval i of m (top 7 mantissa bits) gives
 // invc_i ~ 1/m and ln(c_i) = -ln(invc_i), and
 //   ln(1 + y) = e ln 2 + ln(c_i) + ln(1 + t),  t = m invc_i - 1 + 2^-e (y - (u - 1)) invc_i,
 // the last term restoring what rounding 1 + y lost.  Interval 0 has c = 1, so a
 // small y returns ln(1 + t), t = y, with full relative accuracy; every term
 // is >= 0 otherwise and nothing cancels.  |t| < 2^-7: the Taylor series to t^8
-// leaves 2^-59 of t.  Measured against 80-bit logarithms: at most 1.3 ulp.
+// leaves 2^-59 of t.  Measured against 80-bit logarithms: at most 1.3 ulp, 0.28 in
+// the mean (the library's 0.64 and 0.25).
 #pragma once
 
 #include <hip/hip_runtime.h>
